@@ -98,7 +98,14 @@ constexpr double kFwhmToSigma = 0.42466090014400953;
 constexpr double kLn2 = 0.69314718055994531;
 
 constexpr int kChunk = 64;        // pixels per fringe chunk (one wavefront)
-constexpr int kAdjChunkTile = 32; // chunks per tile of the adjoint fringe grid (with 16 channel groups)
+// Beam cut of the fringe passes, in powers of two: a chunk whose beam at its
+// nearest pixel is below 2^-40 of the beam at the pixel nearest the zenith, at
+// that time and channel, is not visited.  The weight of a Gaussian beam beyond
+// the radius at which it falls to b is b of its total, so what is left out is
+// 2^-40 of the sum's weight, 2^-16 of one FP32 rounding of it; the sky itself
+// carries 2^-24 of its largest value in rounding errors at every pixel, beam
+// centre included, so no sky makes the omitted terms count.
+constexpr float kBeamBits = 40.0f;
 constexpr int kScaleParts = 16;   // row segments of the split forward's sky maxima
 constexpr int kMaxExtent = 16;    // max |lattice difference| supported
 constexpr int kSepPad = 4;        // zero azimuthal columns on each side of the separable T table

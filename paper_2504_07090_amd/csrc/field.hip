@@ -4,6 +4,7 @@
 #include <hip/hip_fp16.h>
 
 #include <algorithm>
+#include <array>
 #include <cstdlib>
 #include <cmath>
 #include <cstdarg>
@@ -202,7 +203,11 @@ struct HostGeometry {
   std::vector<double> p1, p2;            // [t][nv_pad]
   std::vector<float> th2;                // [t][nv_pad]
   std::vector<int> tlo, thi;             // per chunk
-  std::vector<int> tchunk_off, tchunk;   // CSR per time
+  // CSR lists in ascending order of the excess theta^2 of the chunk's nearest
+  // pixel over the nearest pixel of the sky at that time: the chunks up at
+  // each time, and the times at which each chunk is up
+  std::vector<int> tchunk_off, tchunk, ctime_off, ctime;
+  std::vector<float> tchunk_ex, ctime_ex, chunk_ex;   // chunk_ex: a chunk's smallest ctime_ex
   double vis_pix_time = 0.0;             // sum over t of visible pixel count
 };
 
@@ -243,6 +248,96 @@ static void validate_field(const vis_basis* basis, const vis_field_desc* d) {
   }
 }
 
+static double zenith_angle2(double u) {
+  const double th = std::acos(std::min(1.0, u));
+  return th * th;
+}
+
+// Splits pix[lo, hi) into chunks of kChunk pixels that are compact on the sky:
+// halves at a multiple of kChunk along the axis (of the unit vectors) in which
+// the set extends furthest, until one chunk is left.
+static void bisect_chunks(std::vector<int>& pix, size_t lo, size_t hi,
+                          const std::vector<std::array<double, 3>>& s) {
+  if (hi - lo <= static_cast<size_t>(kChunk)) return;
+  std::array<double, 3> mn = s[pix[lo]], mx = mn;
+  for (size_t i = lo; i < hi; ++i)
+    for (int a = 0; a < 3; ++a) {
+      mn[a] = std::min(mn[a], s[pix[i]][a]);
+      mx[a] = std::max(mx[a], s[pix[i]][a]);
+    }
+  int ax = 0;
+  for (int a = 1; a < 3; ++a)
+    if (mx[a] - mn[a] > mx[ax] - mn[ax]) ax = a;
+  const size_t nch = (hi - lo + kChunk - 1) / kChunk, mid = lo + (nch / 2) * kChunk;
+  std::nth_element(pix.begin() + lo, pix.begin() + mid, pix.begin() + hi, [&](int a, int b) {
+    return s[a][ax] != s[b][ax] ? s[a][ax] < s[b][ax] : a < b;
+  });
+  bisect_chunks(pix, lo, mid, s);
+  bisect_chunks(pix, mid, hi, s);
+}
+
+// The pixel of every visible slot.  A chunk of kChunk slots is visited, per
+// time, if any of its pixels is above the horizon and near enough to the beam
+// centre (kBeamBits), so the pixels of a chunk should be close together on the
+// sky: the pixels up at every time go through bisect_chunks.  The pixels that
+// rise or set follow, ordered by the first and the last time they are up, so
+// that a chunk's pixels come up and go down together (a chunk compact on the
+// sky straddles the horizon longer: 61 dishes, 60 times, 0.3% of the visited
+// slots below the horizon instead of 5%); where most pixels rise or set (scans
+// of many hours) all go through bisect_chunks (24 h: 7% below the horizon
+// instead of 29%).  Visited (slot, time) pairs at 61 dishes, 10 deg beam: 26%
+// of those above the horizon (40% in plain pixel order; the pixels themselves
+// are 21%).  The chunks are then sorted by their nearest approach to the beam
+// centre: those near enough at some time are a prefix, and the costliest ones
+// (the most times) come first in every grid.  The pixels left over by a
+// multiple of kChunk, those that stay furthest away, are the last chunk.
+static std::vector<int> order_slots(const vis_basis* basis, int nt, const std::vector<int>& first,
+                                    const std::vector<int>& last, const std::vector<int>& nup,
+                                    const std::vector<double>& near) {
+  const int npix = basis->n_pix, nphi = basis->nphi;
+  std::vector<std::array<double, 3>> s(npix);
+  for (int p = 0; p < npix; ++p) {
+    const double z = -1.0 + (p / nphi + 0.5) * 2.0 / basis->nz, r = std::sqrt(std::max(0.0, 1.0 - z * z));
+    const double al = (p % nphi + 0.5) * 2.0 * kPi / nphi;
+    s[p] = {r * std::cos(al), r * std::sin(al), z};
+  }
+  std::vector<int> up;
+  for (int p = 0; p < npix; ++p)
+    if (nup[p] > 0) up.push_back(p);
+  std::sort(up.begin(), up.end(), [&](int a, int b) { return near[a] != near[b] ? near[a] < near[b] : a < b; });
+  const size_t whole = up.size() / kChunk * kChunk;
+  const std::vector<int> tail(up.begin() + whole, up.end());
+  up.resize(whole);
+  const size_t n_always = std::count_if(up.begin(), up.end(), [&](int p) { return nup[p] == nt; });
+  std::vector<int> pix;
+  if (2 * n_always < up.size()) {
+    pix = up;
+    bisect_chunks(pix, 0, pix.size(), s);
+  } else {
+    std::vector<int> rest;
+    for (int p : up) (nup[p] == nt ? pix : rest).push_back(p);
+    bisect_chunks(pix, 0, pix.size(), s);
+    std::sort(rest.begin(), rest.end(), [&](int a, int b) {
+      return first[a] != first[b] ? first[a] < first[b] : last[a] != last[b] ? last[a] < last[b] : a < b;
+    });
+    pix.insert(pix.end(), rest.begin(), rest.end());
+  }
+  std::vector<std::pair<double, int>> key;
+  for (size_t c = 0; c < whole / kChunk; ++c) {
+    double m = kBelowHorizon;
+    for (int q = 0; q < kChunk; ++q) m = std::min(m, near[pix[c * kChunk + q]]);
+    key.emplace_back(m, static_cast<int>(c));
+  }
+  std::sort(key.begin(), key.end());
+  std::vector<int> out;
+  out.reserve(whole + tail.size());
+  for (const auto& kc : key)
+    out.insert(out.end(), pix.begin() + static_cast<size_t>(kc.second) * kChunk,
+               pix.begin() + static_cast<size_t>(kc.second + 1) * kChunk);
+  out.insert(out.end(), tail.begin(), tail.end());
+  return out;
+}
+
 static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc* d) {
   HostGeometry g;
   const int na = d->n_ant;
@@ -273,93 +368,42 @@ static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc*
   const double cphi = std::cos(d->latitude_rad), sphi = std::sin(d->latitude_rad);
   std::vector<double> E(static_cast<size_t>(nt) * npix), N(E.size()), U(E.size());
   std::vector<int> first(npix, -1), last(npix, -1), nup(npix, 0);   // times above the horizon
-  for (int t = 0; t < nt; ++t)
-    for (int j = 0; j < nz; ++j) {
-      const double z = -1.0 + (j + 0.5) * 2.0 / nz;
-      const double cd = std::sqrt(std::max(0.0, 1.0 - z * z)), sd = z;
+  std::vector<double> zring(nz), cring(nz), cha(nphi), sha(nphi);
+  for (int j = 0; j < nz; ++j) {
+    zring[j] = -1.0 + (j + 0.5) * 2.0 / nz;
+    cring[j] = std::sqrt(std::max(0.0, 1.0 - zring[j] * zring[j]));
+  }
+  // near[p]: the smallest theta^2(p, t) - min_q theta^2(q, t) over the times at
+  // which p is up; th2_near[t]: that minimum, the pixel nearest the zenith
+  std::vector<double> th2_near(nt, kBelowHorizon), near(npix, kBelowHorizon);
+  for (int t = 0; t < nt; ++t) {
+    for (int k = 0; k < nphi; ++k) {
+      const double h = d->lst_rad[t] - (k + 0.5) * 2.0 * kPi / nphi;
+      cha[k] = std::cos(h);
+      sha[k] = std::sin(h);
+    }
+    double umax = -1.0;
+    for (int j = 0; j < nz; ++j)
       for (int k = 0; k < nphi; ++k) {
-        const double alpha = (k + 0.5) * 2.0 * kPi / nphi;
-        const double h = d->lst_rad[t] - alpha;
-        const double ch = std::cos(h), sh = std::sin(h);
-        const size_t o = static_cast<size_t>(t) * npix + j * nphi + k;
-        E[o] = -cd * sh;
-        N[o] = cphi * sd - sphi * cd * ch;
-        U[o] = sphi * sd + cphi * cd * ch;
+        const int p = j * nphi + k;
+        const size_t o = static_cast<size_t>(t) * npix + p;
+        E[o] = -cring[j] * sha[k];
+        N[o] = cphi * zring[j] - sphi * cring[j] * cha[k];
+        U[o] = sphi * zring[j] + cphi * cring[j] * cha[k];
+        umax = std::max(umax, U[o]);
         if (U[o] > 0.0) {
-          const int p = j * nphi + k;
           if (first[p] < 0) first[p] = t;
           last[p] = t;
           ++nup[p];
         }
       }
-    }
-  // Visible slots: the pixels above the horizon at every time first, in pixel
-  // order, then the others ordered by the first and the last time they are
-  // up.  Chunks of 64 slots of the second group then hold pixels that are up
-  // over similar times, so the chunks a time visits (forward) and the times a
-  // chunk visits (adjoint) carry few slots below the horizon, whose terms are
-  // exactly zero (61 dishes, 60 times: 0.3% of the visited slots instead of
-  // 6.8% in plain pixel order).
-  for (int p = 0; p < npix; ++p)
-    if (nup[p] == nt) g.vpix.push_back(p);
-  {
-    std::vector<int> rest;
-    for (int p = 0; p < npix; ++p)
-      if (nup[p] > 0 && nup[p] < nt) rest.push_back(p);
-    std::sort(rest.begin(), rest.end(), [&](int a, int b) {
-      return first[a] != first[b] ? first[a] < first[b] : last[a] != last[b] ? last[a] < last[b] : a < b;
-    });
-    g.vpix.insert(g.vpix.end(), rest.begin(), rest.end());
-  }
-  // The adjoint fringe grid deals tiles of kAdjChunkTile chunks (all
-  // channels) to the XCDs in contiguous ranges and a chunk costs one step per
-  // time in its range, so the chunks are regrouped into tiles of equal mean
-  // cost: longest first, each to the tile of lowest mean so far that has
-  // room.  The last, possibly partial chunk keeps its place (the padding
-  // slots stay at the end).
-  {
-    const int nv0 = static_cast<int>(g.vpix.size());
-    const int nck = (nv0 + kChunk - 1) / kChunk;
-    if (nck > 2) {
-      std::vector<int> cost(nck);
-      for (int c = 0; c < nck; ++c) {
-        int lo = nt, hi = -1;
-        for (int k = c * kChunk; k < std::min(nv0, (c + 1) * kChunk); ++k) {
-          lo = std::min(lo, first[g.vpix[k]]);
-          hi = std::max(hi, last[g.vpix[k]]);
-        }
-        cost[c] = hi - lo + 1;
-      }
-      const int ntile = (nck + kAdjChunkTile - 1) / kAdjChunkTile;
-      std::vector<int> room(ntile, kAdjChunkTile), size(ntile, kAdjChunkTile);
-      size[ntile - 1] = room[ntile - 1] = nck - (ntile - 1) * kAdjChunkTile;
-      std::vector<long> load(ntile, 0);
-      std::vector<std::vector<int>> tiles(ntile);
-      room[ntile - 1] -= 1;                      // the last chunk, placed at the end
-      load[ntile - 1] += cost[nck - 1];
-      std::vector<int> order(nck - 1);
-      for (int c = 0; c < nck - 1; ++c) order[c] = c;
-      std::stable_sort(order.begin(), order.end(), [&](int a, int b) { return cost[a] > cost[b]; });
-      for (int c : order) {
-        int best = -1;
-        for (int tt = 0; tt < ntile; ++tt) {
-          if (room[tt] == 0) continue;
-          // lower mean cost per chunk of the tile's capacity (cross-multiplied)
-          if (best < 0 || load[tt] * size[best] < load[best] * size[tt]) best = tt;
-        }
-        tiles[best].push_back(c);
-        load[best] += cost[c];
-        room[best] -= 1;
-      }
-      tiles[ntile - 1].push_back(nck - 1);
-      std::vector<int> vp;
-      vp.reserve(nv0);
-      for (const auto& tl : tiles)
-        for (int c : tl)
-          for (int k = c * kChunk; k < std::min(nv0, (c + 1) * kChunk); ++k) vp.push_back(g.vpix[k]);
-      g.vpix.swap(vp);
+    if (umax > 0.0) th2_near[t] = zenith_angle2(umax);
+    for (int p = 0; p < npix; ++p) {
+      const double u = U[static_cast<size_t>(t) * npix + p];
+      if (u > 0.0) near[p] = std::min(near[p], zenith_angle2(u) - th2_near[t]);
     }
   }
+  g.vpix = order_slots(basis, nt, first, last, nup, near);
   BV_REQUIRE(!g.vpix.empty(), VIS_EINVAL, "no pixel is above the horizon at any time");
   const int nv = static_cast<int>(g.vpix.size());
   g.nv_pad = static_cast<int>(round_up(nv, kChunk));
@@ -369,12 +413,13 @@ static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc*
   g.th2.assign(g.p1.size(), kBelowHorizon);
   g.tlo.assign(nchunks, nt);
   g.thi.assign(nchunks, -1);
-  std::vector<std::vector<int>> active(nt);
+  // (excess, index) of the chunks up at each time and of the times each chunk is up
+  std::vector<std::vector<std::pair<float, int>>> by_time(nt), by_chunk(nchunks);
   const double* e1 = d->lattice_e1_m;
   const double* e2 = d->lattice_e2_m;
   for (int t = 0; t < nt; ++t) {
     for (int c = 0; c < nchunks; ++c) {
-      bool any = false;
+      double th2_min = kBelowHorizon;
       for (int q = 0; q < kChunk; ++q) {
         const int k = c * kChunk + q;
         if (k >= nv) break;
@@ -383,24 +428,36 @@ static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc*
         g.p1[w] = (e1[0] * E[o] + e1[1] * N[o]) / kCLight;
         g.p2[w] = (e2[0] * E[o] + e2[1] * N[o]) / kCLight;
         if (U[o] > 0.0) {
-          const double th = std::acos(std::min(1.0, U[o]));
-          g.th2[w] = static_cast<float>(th * th);
-          any = true;
+          const double th2 = zenith_angle2(U[o]);
+          g.th2[w] = static_cast<float>(th2);
+          th2_min = std::min(th2_min, th2);
           g.vis_pix_time += 1.0;
         }
       }
-      if (any) {
-        active[t].push_back(c);
+      if (th2_min < kBelowHorizon) {
+        const float ex = static_cast<float>(th2_min - th2_near[t]);
+        by_time[t].emplace_back(ex, c);
+        by_chunk[c].emplace_back(ex, t);
         g.tlo[c] = std::min(g.tlo[c], t);
         g.thi[c] = std::max(g.thi[c], t);
       }
     }
   }
-  g.tchunk_off.push_back(0);
-  for (int t = 0; t < nt; ++t) {
-    for (int c : active[t]) g.tchunk.push_back(c);
-    g.tchunk_off.push_back(static_cast<int>(g.tchunk.size()));
-  }
+  auto flatten = [](std::vector<std::vector<std::pair<float, int>>>& rows, std::vector<int>& off,
+                    std::vector<int>& idx, std::vector<float>& ex) {
+    off.push_back(0);
+    for (auto& r : rows) {
+      std::sort(r.begin(), r.end());
+      for (const auto& v : r) {
+        ex.push_back(v.first);
+        idx.push_back(v.second);
+      }
+      off.push_back(static_cast<int>(idx.size()));
+    }
+  };
+  flatten(by_time, g.tchunk_off, g.tchunk, g.tchunk_ex);
+  flatten(by_chunk, g.ctime_off, g.ctime, g.ctime_ex);
+  for (int c = 0; c < nchunks; ++c) g.chunk_ex.push_back(g.ctime_ex[g.ctime_off[c]]);
   return g;
 }
 
@@ -416,6 +473,11 @@ static void carve_field(vis_field* f, Carver& cv, int n_tchunk) {
   T.chunk_t = cv.take<int2>(f->n_chunks);
   T.tchunk_off = cv.take<int>(nt + 1);
   T.tchunk = cv.take<int>(std::max(1, n_tchunk));
+  T.tchunk_ex = cv.take<float>(std::max(1, n_tchunk));
+  T.ctime_off = cv.take<int>(f->n_chunks + 1);
+  T.ctime = cv.take<int>(std::max(1, n_tchunk));
+  T.ctime_ex = cv.take<float>(std::max(1, n_tchunk));
+  T.chunk_ex = cv.take<float>(f->n_chunks);
   T.bl_ant = cv.take<int2>(f->n_bl);
   T.bl_u = cv.take<int>(f->n_bl);
   T.bl_pos = cv.take<int4>(f->n_bl);
@@ -688,6 +750,7 @@ vis_status vis_field_create(const vis_basis* basis, const vis_field_desc* desc, 
     for (int k = 0; k < f->n_freq; ++k) {
       dnu[k] = static_cast<float>(freq[k] - nu_c);
       sigr[k] = static_cast<float>(desc->beam_ref_hz / freq[k] * kFwhmToSigma);
+      f->sigr_max = std::max(f->sigr_max, sigr[k]);
     }
     auto phase_table = [&](const std::vector<double>& p) {
       std::vector<float2> q(p.size());
@@ -708,6 +771,11 @@ vis_status vis_field_create(const vis_basis* basis, const vis_field_desc* desc, 
     up(T.chunk_t, chunk_t, s);
     up(T.tchunk_off, g.tchunk_off, s);
     up(T.tchunk, g.tchunk, s);
+    up(T.tchunk_ex, g.tchunk_ex, s);
+    up(T.ctime_off, g.ctime_off, s);
+    up(T.ctime, g.ctime, s);
+    up(T.ctime_ex, g.ctime_ex, s);
+    up(T.chunk_ex, g.chunk_ex, s);
     up(T.bl_ant, bl_ant, s);
     up(T.bl_u, bl_u, s);
     up(T.bl_pos, bl_pos, s);

@@ -19,12 +19,12 @@
 // are plain sums taken on the vector ALU.  The fringe x beam tiles exist only
 // in registers and LDS; nothing of size pixels x baselines touches HBM.
 //
-// Phase accuracy: x = nu (e . s) / c is formed in FP64 and reduced to
-// [-1/2, 1/2] before rounding to FP32, and the powers alpha^n, n <= D, come
-// from the three-term recurrence u_{n+1} = 2 cos(theta) u_n - u_{n-1}.  A
-// rounding error made at step k reaches step n multiplied by
-// sin((n - k) theta) / sin(theta), at most n - k in size, so the error of
-// alpha^n stays below about n^2 / 2 FP32 roundings (32 at n = 8).
+// Phase accuracy: x = nu (e . s) / c comes from tables reduced modulo one cycle
+// in FP64 (reduced_cycles), and the powers alpha^n, n <= D, from two chains of
+// the three-term recurrence (lattice_powers).  A rounding error made at step k
+// of a chain reaches step j multiplied by sin((j - k) 2t) / sin(2t), at most
+// j - k in size, so the error of alpha^n stays below about n^2 / 8 FP32
+// roundings (8 at n = 8).
 //
 // The adjoint (transpose over the reals) of the same map, for coefficients
 // omega_u = dL/dRe V_u - i dL/dIm V_u (formed by the gains pass), is
@@ -63,19 +63,6 @@ __device__ __forceinline__ void sincos_rev(float x, float& s, float& c) {
 #endif
 }
 
-// x[l] + x[l ^ 16] and x[l] + x[l ^ 32] with the gfx950 lane-swap instructions
-// (vector ALU; a generic shuffle would go through the LDS crossbar).
-__device__ __forceinline__ float sum_xor16(float x) {
-  const unsigned u = __float_as_uint(x);
-  const auto p = __builtin_amdgcn_permlane16_swap(u, u, false, false);
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
-__device__ __forceinline__ float sum_xor32(float x) {
-  const unsigned u = __float_as_uint(x);
-  const auto p = __builtin_amdgcn_permlane32_swap(u, u, false, false);
-  return __uint_as_float(p[0]) + __uint_as_float(p[1]);
-}
-
 // 2^x on the hardware exponential unit (no denormal-range rescaling: the
 // beam factors it forms are only ever weights, and one below 2^-126 adds
 // nothing to a sum of beam-weighted terms).
@@ -97,6 +84,31 @@ __device__ __forceinline__ V at_u32(const V* base, int k) {
 __device__ __forceinline__ float reduced_cycles(float dnu, float2 q) {
   const float x = __builtin_fmaf(dnu, q.y, q.x);
   return x - __builtin_rintf(x);
+}
+
+// Excess theta^2 beyond which a beam of width sig is cut (kBeamBits).
+__device__ __forceinline__ float beam_cut(float sig) {
+  return kBeamBits * 2.0f * static_cast<float>(kLn2) * sig * sig;
+}
+
+// Number of leading entries of an ascending excess list up to `cut`; the same
+// in every lane.  SEG 64-entry segments load at once.  An undefined cut (NaN)
+// cuts nothing.
+template <int SEG>
+__device__ __forceinline__ int beam_prefix(const float* __restrict__ ex, int n, float cut, int lane) {
+  int cnt = 0;
+  for (int base = 0; base < n; base += 64 * SEG) {
+    float e[SEG];
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) e[q] = ex[min(base + 64 * q + lane, n - 1)];
+    int c = 0;
+#pragma unroll
+    for (int q = 0; q < SEG; ++q)
+      c += __popcll(__ballot(base + 64 * q + lane < n && !(e[q] > cut)));
+    cnt += c;
+    if (c < 64 * SEG) break;
+  }
+  return cnt;
 }
 
 // Block index -> logical index so that consecutive logical indices share an
@@ -141,28 +153,46 @@ __device__ __forceinline__ int lds_at(int px, int col) {
   return px * W + ((((col >> 2) ^ swz<W>(px))) << 2) + (col & 3);
 }
 
-// Powers alpha^n (n = 1..D) and beta^m w (m = 1..D) of one pixel into its LDS
-// rows (row px of As / Bs, zero padding up to W); visit(n, alpha^n, beta^n w)
-// sees every power while it is still in registers.  With alpha = exp(-i t),
-// alpha^(n+1) = 2 cos(t) alpha^n - alpha^(n-1) (the three-term recurrence of
-// cos(n t) and sin(n t)), one FMA per component; the same holds for beta^m w.
+// w a^n, n = 1..D, of a = exp(-i t) from c = cos t, s = sin t, into re[n], im[n]:
+// two interleaved chains of step a^2, u_{n+2} = 2 cos(2t) u_n - u_{n-2} (the
+// three-term recurrence of cos(n t) and sin(n t)), one FMA per component.  A
+// rounding error grows over n / 2 steps instead of the n of a chain of step a.
+// cos(2t) comes from the smaller of |s| and |c|, which the hardware unit gives
+// with the smaller absolute error (2.3e-8 against 4.6e-8 rms, measured) and
+// whose square damps it further.
+template <int D>
+__device__ __forceinline__ void lattice_powers(float c, float s, float w, float* re, float* im) {
+  const bool small_s = fabsf(s) < fabsf(c);
+  const float m = small_s ? s : c;
+  const float h = __builtin_fmaf(-2.f * m, m, 1.f), c2 = small_s ? h : -h, t = 2.f * c2;
+  re[1] = c * w;
+  im[1] = -s * w;
+  re[2] = c2 * w;
+  im[2] = -2.f * s * re[1];
+#pragma unroll
+  for (int n = 3; n <= D; ++n) {
+    // u_{-1} = conj(u_1), u_0 = w
+    re[n] = t * re[n - 2] - (n == 3 ? re[1] : n == 4 ? w : re[n - 4]);
+    im[n] = t * im[n - 2] - (n == 3 ? -im[1] : n == 4 ? 0.f : im[n - 4]);
+  }
+}
+
+// Powers alpha^n (n = 1..D) and beta^m w (m = 1..D) of one pixel into av, bv;
+// visit(n, alpha^(n+1), beta^(n+1) w) sees every power while it is still in
+// registers.
 template <int D, class Visit>
 __device__ __forceinline__ void powers_f32(float* av, float* bv, float c1, float s1, float c2,
                                            float s2, float w, Visit visit) {
-  float ar0 = 1.f, ai0 = 0.f, ar = c1, ai = -s1;
-  float br0 = w, bi0 = 0.f, br = c2 * w, bi = -s2 * w;
-  const float t1 = 2.f * c1, t2 = 2.f * c2;
+  float ar[D + 1], ai[D + 1], br[D + 1], bi[D + 1];
+  lattice_powers<D>(c1, s1, 1.f, ar, ai);
+  lattice_powers<D>(c2, s2, w, br, bi);
 #pragma unroll
   for (int n = 0; n < D; ++n) {
-    av[2 * n] = ar;
-    av[2 * n + 1] = ai;
-    bv[2 * n] = br;
-    bv[2 * n + 1] = bi;
-    visit(n, ar, ai, br, bi);
-    const float nar = t1 * ar - ar0, nai = t1 * ai - ai0;
-    const float nbr = t2 * br - br0, nbi = t2 * bi - bi0;
-    ar0 = ar; ai0 = ai; br0 = br; bi0 = bi;
-    ar = nar; ai = nai; br = nbr; bi = nbi;
+    av[2 * n] = ar[n + 1];
+    av[2 * n + 1] = ai[n + 1];
+    bv[2 * n] = br[n + 1];
+    bv[2 * n + 1] = bi[n + 1];
+    visit(n, ar[n + 1], ai[n + 1], br[n + 1], bi[n + 1]);
   }
 }
 template <int W>
@@ -174,16 +204,6 @@ __device__ __forceinline__ void store_rows(float* As, float* Bs, int px, const f
     *reinterpret_cast<f4*>(Bs + o) = f4{bv[4 * g], bv[4 * g + 1], bv[4 * g + 2], bv[4 * g + 3]};
   }
 }
-template <int D, int W, class Visit>
-__device__ __forceinline__ void write_powers(float* As, float* Bs, int px, float c1, float s1,
-                                             float c2, float s2, float w, Visit visit) {
-  float av[W], bv[W];
-  powers_f32<D>(av, bv, c1, s1, c2, s2, w, visit);
-#pragma unroll
-  for (int r = 2 * D; r < W; ++r) av[r] = bv[r] = 0.f;
-  store_rows<W>(As, Bs, px, av, bv);
-}
-
 // ------------------------------------------------- split-precision helpers --
 // Split-precision fields run the fringe products on FP16 MFMA as hi + lo
 // pairs (x ~ hi + lo, hi = fp16(x), lo = fp16(x - hi)), three products
@@ -228,25 +248,21 @@ template <int W> struct SplitRows {
   static constexpr int BL_WORDS = (W / 4) * BLP;
 };
 
-// Powers of one pixel for the split adjoint: alpha^n in FP32 into its As row
-// (as write_powers), beta^m as FP16 hi + lo pairs into its Bh / Bl rows.
+// Powers of one pixel for the split adjoint: alpha^n in FP32 (as powers_f32),
+// beta^m as FP16 hi + lo pairs.
 template <int D, class Visit>
 __device__ __forceinline__ void powers_split_adj(float* av, uint32_t* bh, uint32_t* bl, float c1,
                                                  float s1, float c2, float s2, Visit visit) {
-  float ar0 = 1.f, ai0 = 0.f, ar = c1, ai = -s1;
-  float br0 = 1.f, bi0 = 0.f, br = c2, bi = -s2;
-  const float t1 = 2.f * c1, t2 = 2.f * c2;
+  float ar[D + 1], ai[D + 1], br[D + 1], bi[D + 1];
+  lattice_powers<D>(c1, s1, 1.f, ar, ai);
+  lattice_powers<D>(c2, s2, 1.f, br, bi);
 #pragma unroll
   for (int n = 0; n < D; ++n) {
-    av[2 * n] = ar;
-    av[2 * n + 1] = ai;
-    bh[n] = split_hi2(br, bi);
-    bl[n] = split_lo2(br, bi, bh[n]);
-    visit(n, ar, ai, br, bi);
-    const float nar = t1 * ar - ar0, nai = t1 * ai - ai0;
-    const float nbr = t2 * br - br0, nbi = t2 * bi - bi0;
-    ar0 = ar; ai0 = ai; br0 = br; bi0 = bi;
-    ar = nar; ai = nai; br = nbr; bi = nbi;
+    av[2 * n] = ar[n + 1];
+    av[2 * n + 1] = ai[n + 1];
+    bh[n] = split_hi2(br[n + 1], bi[n + 1]);
+    bl[n] = split_lo2(br[n + 1], bi[n + 1], bh[n]);
+    visit(n, ar[n + 1], ai[n + 1], br[n + 1], bi[n + 1]);
   }
 }
 template <int W>
@@ -268,20 +284,6 @@ __device__ __forceinline__ void store_rows_split_adj(float* As, uint32_t* Bh, ui
   for (int g = 0; g < W / 4; ++g)
     *reinterpret_cast<u2*>(Bl + g * R::BLP + 2 * px) = u2{bl[2 * g], bl[2 * g + 1]};
 }
-template <int D, int W, class Visit>
-__device__ __forceinline__ void write_powers_split(float* As, uint32_t* Bh, uint32_t* Bl, int px,
-                                                   float c1, float s1, float c2, float s2,
-                                                   Visit visit) {
-  float av[W];
-  uint32_t bh[W / 2], bl[W / 2];
-  powers_split_adj<D>(av, bh, bl, c1, s1, c2, s2, visit);
-#pragma unroll
-  for (int r = 2 * D; r < W; ++r) av[r] = 0.f;
-#pragma unroll
-  for (int n = D; n < W / 2; ++n) bh[n] = bl[n] = 0u;
-  store_rows_split_adj<W>(As, Bh, Bl, px, av, bh, bl);
-}
-
 // Forward split rows: each pixel row holds W halves (W / 2 words, pairs
 // (Re, Im) of one power) in 16-byte groups, group g stored at g ^ swz_h(px)
 // so that a wavefront's 16-byte row writes spread over the banks; four
@@ -312,20 +314,16 @@ template <int D, class Visit>
 __device__ __forceinline__ void powers_split_fwd(uint32_t* ah, uint32_t* al, uint32_t* bh, uint32_t* bl,
                                                  float c1, float s1, float c2, float s2, float w,
                                                  Visit visit) {
-  float ar0 = 1.f, ai0 = 0.f, ar = c1, ai = -s1;
-  float br0 = w, bi0 = 0.f, br = c2 * w, bi = -s2 * w;
-  const float t1 = 2.f * c1, t2 = 2.f * c2;
+  float ar[D + 1], ai[D + 1], br[D + 1], bi[D + 1];
+  lattice_powers<D>(c1, s1, 1.f, ar, ai);
+  lattice_powers<D>(c2, s2, w, br, bi);
 #pragma unroll
   for (int n = 0; n < D; ++n) {
-    ah[n] = split_hi2(ar, ai);
-    al[n] = split_lo2(ar, ai, ah[n]);
-    bh[n] = split_hi2(br, bi);
-    bl[n] = split_lo2(br, bi, bh[n]);
-    visit(n, ar, ai, br, bi);
-    const float nar = t1 * ar - ar0, nai = t1 * ai - ai0;
-    const float nbr = t2 * br - br0, nbi = t2 * bi - bi0;
-    ar0 = ar; ai0 = ai; br0 = br; bi0 = bi;
-    ar = nar; ai = nai; br = nbr; bi = nbi;
+    ah[n] = split_hi2(ar[n + 1], ai[n + 1]);
+    al[n] = split_lo2(ar[n + 1], ai[n + 1], ah[n]);
+    bh[n] = split_hi2(br[n + 1], bi[n + 1]);
+    bl[n] = split_lo2(br[n + 1], bi[n + 1], bh[n]);
+    visit(n, ar[n + 1], ai[n + 1], br[n + 1], bi[n + 1]);
   }
 }
 template <int W>
@@ -417,8 +415,8 @@ __device__ __forceinline__ float chan_scale(const float* part, int f, float d_om
 // ------------------------------------------------------------------ forward --
 // One block of kFwdWaves wavefronts per (t, nu) (per (t, group of stacked
 // channels) for D <= 4, see fwd_channels_per_tile); wave w takes every
-// kFwdWaves-th pixel chunk visible at t, starting at chunk w, and the block
-// adds the waves' partial tiles in a fixed order at the end.  Splitting a
+// kFwdWaves-th pixel chunk within the beam at t (kBeamBits), starting at chunk
+// w, and the block adds the waves' partial tiles in a fixed order at the end.  Splitting a
 // (t, nu) over the four SIMDs of a CU balances the SIMDs: with one wave per
 // (t, nu), a 61-dish field's 3840 waves over 1024 SIMDs leave a quarter of
 // the SIMDs with 4 waves and the rest with 3, and the kernel lasts as long
@@ -426,7 +424,13 @@ __device__ __forceinline__ float chan_scale(const float* part, int f, float d_om
 // are read from LDS into registers, then the 16 MFMAs of chunk k are
 // interleaved with the vector-ALU generation of the wave's next chunk
 // (written to LDS); geometry is loaded two of the wave's chunks ahead.  Four
-// resident waves per SIMD (<= 128 VGPRs) for extents up to 8.
+// resident waves per SIMD (<= 128 VGPRs) for extents up to 8.  Bound by issue
+// (FP32 MFMA and vector ALU take turns).  Visiting only the chunks within the
+// beam leaves 27% of the (chunk, time) pairs above the horizon at 61 dishes, 64
+// channels, 60 times, a 10 deg beam: 0.606 -> 0.178 ms (0.162 at the same time
+// per chunk; the rest is the start and end of each block).  With a 35 deg beam,
+// where every chunk is within it, the more accurate powers and the list cost
+// 2% (37 dishes, 40 channels, 30 times: 0.200 -> 0.205 ms).
 constexpr int kFwdWaves = 4;
 
 struct FwdArgs {
@@ -439,6 +443,7 @@ struct FwdArgs {
   const float* TH2;
   const int* tchunk_off;
   const int* tchunk;
+  const float* tchunk_ex;
   const int2* ubl_nm;
   const float* img;
   const float* fwhm;
@@ -506,7 +511,7 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
   tile_map(L, nt, nfg, 4, 32, t, fgrp);   // 128 resident blocks per XCD: 4 times x 32 channel groups
   // channel c of the group: f = NCH fgrp + c; one past the band (an odd
   // channel count) runs with zero weight and is not written
-  float dnu[NCH], csc[NCH], kb[NCH], chan_on[NCH];
+  float dnu[NCH], csc[NCH], kb[NCH], chan_on[NCH], cut = 0.f;
   const float* imf[NCH];
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
@@ -516,6 +521,7 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
     csc[c] = SPLIT ? chan_scale(args.cscale, fl, d_omega) : 1.0f;   // power of two
     const float sig = fwhm[0] * args.sigr[fl];
     kb[c] = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
+    cut = c == 0 ? beam_cut(sig) : fmaxf(cut, beam_cut(sig));
     imf[c] = img + static_cast<size_t>(fl) * nvp;
   }
 
@@ -538,14 +544,18 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
 #pragma unroll
     for (int n = 0; n < DX; ++n) axr[c][n] = axi[c][n] = bxr[c][n] = bxi[c][n] = 0.f;
 
-  const int cbeg = tchunk_off[t], cend = tchunk_off[t + 1];
+  // the chunks of this time within the beam of the group's widest channel,
+  // visited from the furthest to the nearest: the sums take the small terms
+  // first (nearest first, their rounding errors measured 1.2 to 2 times larger)
+  const int cbeg = tchunk_off[t];
+  const int cend = cbeg + beam_prefix<8>(args.tchunk_ex + cbeg, tchunk_off[t + 1] - cbeg, cut, lane);
   const float2* q1t = Q1 + static_cast<size_t>(t) * nvp;
   const float2* q2t = Q2 + static_cast<size_t>(t) * nvp;
   const float* tht = TH2 + static_cast<size_t>(t) * nvp;
 
   struct G { float2 q1, q2; float th, iv[NCH]; };
   auto load = [&](int ci) {
-    const int k = tchunk[ci] * kChunk + lane;
+    const int k = tchunk[cbeg + cend - 1 - ci] * kChunk + lane;
     G g;
     g.q1 = at_u32(q1t, k);
     g.q2 = at_u32(q2t, k);
@@ -554,9 +564,8 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
     for (int c = 0; c < NCH; ++c) g.iv[c] = at_u32(imf[c], k);
     return g;
   };
-  // powers of one chunk into LDS, channel c in rows and columns 2D c ..;
-  // `live` = 0 turns a padding pass into a no-op
-  auto generate = [&](const G& g, float live) {
+  // powers of one chunk into LDS, channel c in rows and columns 2D c ..
+  auto generate = [&](const G& g) {
     float av[SPLIT ? 1 : W], bv[SPLIT ? 1 : W];
     uint32_t ah[SPLIT ? W / 2 : 1], al[SPLIT ? W / 2 : 1], bh[SPLIT ? W / 2 : 1], bl[SPLIT ? W / 2 : 1];
     float wlast = 0.f;   // the weight (times its scale) of the last channel
@@ -564,7 +573,7 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
     for (int c = 0; c < NCH; ++c) {
       const float x1 = reduced_cycles(dnu[c], g.q1);
       const float x2 = reduced_cycles(dnu[c], g.q2);
-      const float s = live * chan_on[c] * d_omega * beam_exp2(-g.th * kb[c]) * g.iv[c];
+      const float s = chan_on[c] * d_omega * beam_exp2(-g.th * kb[c]) * g.iv[c];
       float s1, c1, s2, c2;
       sincos_rev(x1, s1, c1);
       sincos_rev(x2, s2, c2);
@@ -637,16 +646,7 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
       }
     }
   };
-  // one chunk: the MFMAs of chunk ci (register operands) interleaved with the
-  // generation of chunk ci + 1 from `cur`, while chunk ci + 2's geometry loads
-  // into `nxt`; the loop below is unrolled by two so the two geometry sets
-  // swap roles without register copies
-  constexpr int S = kFwdWaves;   // chunk stride of one wave
-  auto chunk_step = [&](int ci, const G& cur, G& nxt) {
-    nxt = load(min(ci + 2 * S, cend - 1));
-    // keep the prefetch here: the sources are read-only, so the optimizer
-    // would otherwise re-issue the loads right before their use
-    asm volatile("" ::: "memory");
+  auto products = [&]() {
     if constexpr (SPLIT) {
 #pragma unroll
       for (int ks = 0; ks < 2; ++ks)
@@ -667,7 +667,19 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
           for (int j = 0; j < RT; ++j)
             acc[q % NACC][i][j] = mfma4(a[q][i], b[q][j], acc[q % NACC][i][j]);
     }
-    generate(cur, ci + S < cend ? 1.0f : 0.0f);
+  };
+  // one chunk but the wave's last: the MFMAs of chunk ci (register operands)
+  // interleaved with the generation of the wave's next chunk from `cur`, while
+  // the geometry of the one after it loads into `nxt`; the loop below is
+  // unrolled by two so the two geometry sets swap roles without register copies
+  constexpr int S = kFwdWaves;   // chunk stride of one wave
+  auto chunk_step = [&](int ci, const G& cur, G& nxt) {
+    nxt = load(min(ci + 2 * S, cend - 1));
+    // keep the prefetch here: the sources are read-only, so the optimizer
+    // would otherwise re-issue the loads right before their use
+    asm volatile("" ::: "memory");
+    products();
+    generate(cur);
     if constexpr (SPLIT) {
 #pragma unroll
       for (int q = 0; q < 6 * RT * RT; ++q) {
@@ -689,41 +701,63 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
   };
   const int c0 = cbeg + wv;
   if (c0 < cend) {   // uniform over the wave
-    generate(load(c0), 1.0f);
+    generate(load(c0));
     G ga = load(min(c0 + S, cend - 1)), gb;
     wave_sync();
     operands();
     wave_sync();
-    for (int ci = c0; ci < cend; ci += 2 * S) {
+    int ci = c0;
+    if (((cend - 1 - c0) / S) & 1) {   // an odd number of steps before the last chunk
       chunk_step(ci, ga, gb);
-      if (ci + S >= cend) break;
+      ga = gb;
+      ci += S;
+    }
+    for (; ci + S < cend; ci += 2 * S) {
+      chunk_step(ci, ga, gb);
       chunk_step(ci + S, gb, ga);
     }
+    products();
   }
-  // channel of each tile row / column block (its scale is undone on its block)
   float inv_csc[NCH];
 #pragma unroll
-  for (int c = 0; c < NCH; ++c) {
-    inv_csc[c] = 1.0f / csc[c];   // exact: a power of two
-    if constexpr (!AXT) {
+  for (int c = 0; c < NCH; ++c) inv_csc[c] = 1.0f / csc[c];   // exact: a power of two
+  // Axis sums over the lanes of all waves: every lane's NAX partial sums go to
+  // the operand rows value by value, and eight threads per value add them in a
+  // fixed order (a butterfly over the lanes, 6 NAX cross-lane moves per wave,
+  // costs as much as two chunks).
+  constexpr int NAX = AXT ? 0 : 4 * D * NCH;
+  constexpr int NAXT = (NAX + 31) / 32;   // values per thread group
+  float axs[NAXT > 0 ? NAXT : 1];
+  if constexpr (!AXT) {
+    static_assert(NAX == 2 * W, "axis sums fill the operand rows");
+#pragma unroll
+    for (int c = 0; c < NCH; ++c)
 #pragma unroll
       for (int n = 0; n < D; ++n) {
+        const float v[4] = {axr[c][n], axi[c][n], bxr[c][n] * inv_csc[c], bxi[c][n] * inv_csc[c]};
 #pragma unroll
-        for (int o = 32; o >= 1; o >>= 1) {
-          axr[c][n] += __shfl_xor(axr[c][n], o);
-          axi[c][n] += __shfl_xor(axi[c][n], o);
-          bxr[c][n] += __shfl_xor(bxr[c][n], o);
-          bxi[c][n] += __shfl_xor(bxi[c][n], o);
-        }
-        if constexpr (SPLIT) {
-          bxr[c][n] *= inv_csc[c];
-          bxi[c][n] *= inv_csc[c];
+        for (int q = 0; q < 4; ++q) {
+          const int e = 4 * (D * c + n) + q;
+          (e < W ? As + 64 * e : Bs + 64 * (e - W))[lane] = v[q];
         }
       }
+    __syncthreads();
+#pragma unroll
+    for (int g = 0; g < NAXT; ++g) {
+      const int e = 32 * g + (threadIdx.x >> 3), part = threadIdx.x & 7;
+      float sum = 0.f;
+#pragma unroll
+      for (int w = 0; w < kFwdWaves; ++w) {
+        const float* x = (e < W ? As_all[w] + 64 * e : Bs_all[w] + 64 * (e - W)) + 8 * part;
+        const f4 x0 = *reinterpret_cast<const f4*>(x), x1 = *reinterpret_cast<const f4*>(x + 4);
+        sum += ((x0[0] + x0[1]) + (x0[2] + x0[3])) + ((x1[0] + x1[1]) + (x1[2] + x1[3]));
+      }
+      for (int o = 1; o < 8; o <<= 1) sum += __shfl_xor(sum, o);
+      axs[g] = sum;
     }
+    __syncthreads();
   }
-  // this wave's P tile to its LDS rows (reused as a W x W matrix), its axis
-  // sums to its Bs rows
+  // this wave's P tile to its LDS rows (reused as a W x W matrix)
   {
     float* Pw = As;
 #pragma unroll
@@ -745,31 +779,22 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
           }
           Pw[(16 * i + 4 * (lane >> 4) + r) * W + 16 * j + (lane & 15)] = sum;
         }
-    float* AXw = Bs;  // [NCH][D][4]: axr, axi, bxr, bxi
-    if (!AXT && lane == 0) {
-#pragma unroll
-      for (int c = 0; c < NCH; ++c)
-#pragma unroll
-        for (int n = 0; n < DX; ++n) {
-          AXw[4 * (D * c + n)] = axr[c][n];
-          AXw[4 * (D * c + n) + 1] = axi[c][n];
-          AXw[4 * (D * c + n) + 2] = bxr[c][n];
-          AXw[4 * (D * c + n) + 3] = bxi[c][n];
-        }
-    }
   }
   __syncthreads();
-  // the block's totals, waves added in index order, into the last wave's
-  // rows beyond the tiles (W x W + 4 D NCH floats fit in one wave's 64 W)
-  constexpr int NAX = AXT ? 0 : 4 * D * NCH;
-  float* P = Bs_all[kFwdWaves - 1] + NAX;
-  float* AX = Bs_all[kFwdWaves - 1] + NAX + W * W;
-  static_assert(2 * NAX + W * W <= 64 * W, "tile totals exceed one wave's rows");
-  for (int e = threadIdx.x; e < W * W + NAX; e += 64 * kFwdWaves) {
+  // the block's totals, waves added in index order, into the last wave's rows
+  float* P = Bs_all[kFwdWaves - 1];
+  float* AX = P + W * W;   // [NCH][D][4]: axr, axi, bxr, bxi
+  static_assert(NAX + W * W <= 64 * W, "tile totals exceed one wave's rows");
+  for (int e = threadIdx.x; e < W * W; e += 64 * kFwdWaves) {
     float sum = 0.f;
 #pragma unroll
-    for (int w = 0; w < kFwdWaves; ++w) sum += e < W * W ? As_all[w][e] : Bs_all[w][e - W * W];
-    if (e < W * W) P[e] = sum; else AX[e - W * W] = sum;
+    for (int w = 0; w < kFwdWaves; ++w) sum += As_all[w][e];
+    P[e] = sum;
+  }
+  if constexpr (!AXT) {
+#pragma unroll
+    for (int g = 0; g < NAXT; ++g)
+      if ((threadIdx.x & 7) == 0) AX[32 * g + (threadIdx.x >> 3)] = axs[g];
   }
   __syncthreads();
 #pragma unroll
@@ -803,12 +828,23 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
 }
 
 // ------------------------------------------------------------------ adjoint --
-// One wavefront per (nu, chunk of 64 visible pixels) (per pair of channels
-// for D = 4, see adj_channels_per_tile); loops over the times at which the
-// chunk is above the horizon.  gco[t][nu] holds the coefficient
-// matrix in MFMA A-operand order, then the alpha-axis accumulator inputs of
-// every (row tile, lane group), then the axis coefficients (and, SPLIT, the
-// inverse of the power-of-two scale of the FP16 coefficients).
+// One block per (nu, chunk of 64 visible pixels) (per pair of channels
+// for D = 4, see adj_channels_per_tile); its wavefronts loop over the times at
+// which the chunk is above the horizon and within the beam (kBeamBits).
+// gco[t][nu] holds the coefficient matrix in MFMA A-operand order, then the
+// alpha-axis accumulator inputs of every (row tile, lane group), then the axis
+// coefficients (and, SPLIT, the inverse of the power-of-two scale of the FP16
+// coefficients).
+//
+// Bound by issue, like the forward.  61 dishes, 64 channels, 60 times, 10 deg
+// beam: 0.660 -> 0.212 ms for 27% of the (chunk, time) pairs.  What is left
+// over the 0.176 ms of the same time per pair is each wave's start and end
+// (about 200 vector instructions, two steps' worth).  Tried: one wave per item
+// at every beam width (0.245 ms: 8400 items within the beam in 4096 resident
+// waves of unequal length leave CUs idle at the end, 72% of the CU cycles
+// busy), two waves (0.215 ms), and resident blocks that take items in rounds
+// (0.236 ms); with a 35 deg beam one wave per item is the fastest (37 dishes:
+// 0.210 ms against 0.227 ms with four waves), hence the rule on the items.
 //
 // SPLIT: T = G Bb runs on FP16 MFMA, per 16 x 16 tile one K = 32 product
 // [G_hi | G_lo] [B_hi; B_hi] and one K = 16 product G_hi B_lo; the coefficient
@@ -824,7 +860,13 @@ struct AdjArgs {
   const float2* Q1;
   const float2* Q2;
   const float* TH2;
-  const int2* chunk_t;
+  const float* chunk_ex;
+  float sigr_max;
+  int split_chunks;
+  unsigned nfg_magic;   // ceil(2^32 / channel groups)
+  const int* ctime_off;
+  const int* ctime;
+  const float* ctime_ex;
   const float* img;
   const float* fwhm;
   const float* gco;
@@ -838,10 +880,15 @@ struct AdjArgs {
   int nv, fstride;
 };
 
+// Wavefronts per block, and the rounds of resident waves that the items within
+// the beam must exceed for each wave to take whole items.
+__host__ __device__ constexpr int adj_waves(int D) { return D <= 8 ? 4 : 2; }
+constexpr int kAdjRounds = 3;
+
 template <int D, bool SPLIT>
 struct KFringeAdj {
   using Args = AdjArgs;
-  static constexpr int kThreads = 64, kWaves = 1;
+  static constexpr int kThreads = 64 * adj_waves(D), kWaves = 1;
   static __device__ void run(const AdjArgs& args, const Blk& B);
 };
 
@@ -852,7 +899,6 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
   const float2* Q1 = args.Q1;
   const float2* Q2 = args.Q2;
   const float* TH2 = args.TH2;
-  const int2* __restrict__ chunk_t = args.chunk_t;
   const float* __restrict__ img = args.img;
   const float* __restrict__ fwhm = args.fwhm;
   const float* __restrict__ gco = args.gco;
@@ -863,31 +909,65 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
   using R = SplitRows<T::W>;
   constexpr int RT = T::RT, W = T::W;
   constexpr int NMAT = RT * RT * (SPLIT ? 384 : 256);
-  __shared__ __attribute__((aligned(16))) float As[64 * W];
+  constexpr int NW = adj_waves(D);
+  __shared__ __attribute__((aligned(16))) float As_all[NW][64 * W];
   // FP32 B operand rows, or (SPLIT) the hi rows followed by the lo rows
-  __shared__ __attribute__((aligned(16))) float Bs[SPLIT ? 64 * R::BH + R::BL_WORDS : 64 * W];
+  __shared__ __attribute__((aligned(16))) float Bs_all[NW][SPLIT ? 64 * R::BH + R::BL_WORDS : 64 * W];
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);   // wave-uniform
+  float* As = As_all[wv];
+  float* Bs = Bs_all[wv];
   uint32_t* Bh = reinterpret_cast<uint32_t*>(Bs);
   uint32_t* Bl = Bh + 64 * R::BH;
-  const int lane = threadIdx.x;
+  const int lane = threadIdx.x & 63;
   constexpr int NCH = adj_channels_per_tile(D);
   static_assert(NCH == 1 || (D == 4 && RT == 1), "two stacked channels: D = 4 only");
   // beta-axis terms in the tile's row 2 D (the gains pass put omega(0, m)
   // there) against a row of ones in the pixel operand
   constexpr bool AXT = adj_axis_in_tile(D);
   const int nfg = (nf + NCH - 1) / NCH;   // channel groups
-  const int L = xcd_logical(B.x, B.nx);
-  if (L >= nfg * nchunks) return;
-  int chunk, fgrp;
-  // 512 resident waves per XCD: 32 chunks x 16 channel groups (the field
-  // set-up orders the chunks so that every 32-chunk tile holds about the
-  // same number of (chunk, time) steps, so the XCDs' ranges balance)
-  tile_map(L, nchunks, nfg, kAdjChunkTile, 16, chunk, fgrp);
-  const int k = chunk * kChunk + lane;
+  // dL/dI of this lane's pixel of a chunk
+  auto put = [&](int chunk, int f, float v) {
+    const int k = chunk * kChunk + lane;
+    if (args.dfull != nullptr) {        // uniform over the wave
+      if (k < args.nv)
+        args.dfull[static_cast<size_t>(args.voff[k]) + static_cast<size_t>(f) * args.fstride] = v;
+    } else {
+      dimg[static_cast<size_t>(f) * nvp + k] = v;
+    }
+  };
   const float fw = fwhm[0];
+  const float cut_w = beam_cut(fw * args.sigr_max);   // the field's widest channel
+  // Items are (chunk, channel group) pairs, chunk-major.  The chunks come
+  // sorted by their nearest approach to the beam centre: those within the beam
+  // of the field's widest channel are a prefix, the longest time loops start
+  // first, and the grid ends on items that only write zeros.  With few items
+  // within the beam (at most split_chunks chunks) the block's waves share one
+  // item's times; with many, each wave takes an item of its own.
+  const bool shared = args.split_chunks >= nchunks || args.chunk_ex[args.split_chunks] > cut_w;
+  const int item = shared ? B.x : B.x * NW + wv;
+  if (item >= nfg * nchunks) return;
+  // item / nfg through the host's ceil(2^32 / nfg) (at most one too large), on
+  // the scalar unit
+  int chunk = nfg == 1 ? item : static_cast<int>(__umulhi(static_cast<unsigned>(item), args.nfg_magic));
+  if (chunk * nfg > item) --chunk;
+  const int fgrp = item - chunk * nfg;
+  if (args.chunk_ex[chunk] > cut_w) {   // uniform over the wave
+    if (!shared || wv == 0)
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) {
+        const int f = NCH * fgrp + c;
+        if (f >= nf) break;
+        put(chunk, f, 0.f);
+        if (lane == 0) f_part[static_cast<size_t>(f) * nchunks + chunk] = 0.f;
+      }
+    return;
+  }
+  const int w0 = shared ? wv : 0, nw = shared ? NW : 1;   // this wave's share of the times
+  const int k = chunk * kChunk + lane;
   // channel c of the group: f = NCH fgrp + c (one past the band, for an odd
   // channel count, gets zero coefficients and is not written)
   int fch[NCH];
-  float dnu[NCH], kb[NCH], kappa[NCH], ival[NCH], acc_i[NCH], acc_f[NCH], chan_on[NCH];
+  float dnu[NCH], kb[NCH], acc_i[NCH], acc_f[NCH], chan_on[NCH], cut = 0.f;
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     const int fc = NCH * fgrp + c;
@@ -896,8 +976,7 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
     dnu[c] = args.dnu[fch[c]];
     const float sig = fw * args.sigr[fch[c]];
     kb[c] = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
-    kappa[c] = 1.0f / (sig * sig * fw);   // dB/dF = B theta^2 kappa
-    ival[c] = img[static_cast<size_t>(fch[c]) * nvp + k];
+    cut = c == 0 ? beam_cut(sig) : fmaxf(cut, beam_cut(sig));
     acc_i[c] = acc_f[c] = 0.f;
   }
   // NCH > 1: the tile's row block r / 2D and column block belong to one
@@ -906,12 +985,19 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
   // its output rows 4 (lane >> 4) .. + 3 belong to channel (lane >> 4) / 2
   const int c_row = NCH > 1 ? (lane & 15) / (2 * D) : 0;
   const int c_out = NCH > 1 ? (lane >> 4) / (D / 2) : 0;
-  const int2 tr = chunk_t[chunk];
+  // the times at which this chunk is within the beam of the group's widest channel
+  const int tbeg = args.ctime_off[chunk], tall = args.ctime_off[chunk + 1] - tbeg;
+  const int* __restrict__ tlist = args.ctime + tbeg;
+  // 64 entries of the list in the lanes: the first ones load beside their excesses
+  int tl = tlist[min(lane, tall - 1)], tl_blk = 0;
+  const int ntl = beam_prefix<1>(args.ctime_ex + tbeg, tall, cut, lane);
+  const int mine = shared ? max(0, (ntl - wv + NW - 1) / NW) : ntl;   // entries w0, w0 + nw, ..
   // Partial sums, over this lane's four rows of every row tile, of the core and
   // alpha-axis terms of the pixels of the four 16-pixel groups, weighted by B
   // and by B theta^2; reduced across the row groups once, after the time loop.
   float pz_i[4] = {0.f, 0.f, 0.f, 0.f}, pz_f[4] = {0.f, 0.f, 0.f, 0.f};
-  __shared__ float2 BW[NCH][64];   // (B, B theta^2) of every pixel of the chunk at this t
+  __shared__ float2 BW_all[NW][NCH][64];   // (B, B theta^2) of every pixel of the chunk at this t
+  float2 (*BW)[64] = BW_all[wv];
   const size_t gst = static_cast<size_t>(nf) * gstride;
   // gco feeds the wave-uniform (scalar) loads of the axis coefficients;
   // gco_lane, the same table, the per-lane loads of the prefetch below: a
@@ -920,8 +1006,9 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
   auto gco_at = [&](int t, int c) { return gco + t * gst + static_cast<size_t>(fch[c]) * gstride; };
   // Software pipeline over t, unrolled by two so that the two register sets
   // swap roles without copies: the geometry and this lane's coefficients of
-  // time t + 1 load while time t is processed.
+  // the next time load while one is processed.
   struct Step : AdjCoef<RT, SPLIT> {
+    int t;
     float2 q1, q2;
     float th2;
     // alpha-axis coefficients of this lane's rows 16 i + 4 (lane >> 4) + 0..3:
@@ -932,7 +1019,19 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
   };
   // per-lane channel selection (NCH <= 2)
   auto chan_of = [&](const int* arr, int c) { return NCH == 1 || c == 0 ? arr[0] : arr[NCH - 1]; };
-  auto load_step = [&](Step& S, int t) {
+  // entry i of this wave's share, from its end (the weakest beam first, as in
+  // the forward)
+  auto time_at = [&](int i) {   // uniform
+    const int e = ntl - 1 - w0 - i * nw;
+    if ((e >> 6) != tl_blk) {
+      tl_blk = e >> 6;
+      tl = tlist[min(64 * tl_blk + lane, tall - 1)];
+    }
+    return __builtin_amdgcn_readlane(tl, e & 63);
+  };
+  auto load_step = [&](Step& S, int i) {
+    const int t = time_at(i);
+    S.t = t;
     const size_t row = static_cast<size_t>(t) * nvp;   // uniform over the wave
     S.q1 = at_u32(Q1 + row, k);
     S.q2 = at_u32(Q2 + row, k);
@@ -957,19 +1056,20 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
           S.ga[i][kt] = on_k32 ? va : h8{};
           S.gb[i][kt] = on_blk ? vb : h4{};
         } else {
-          const f4 v = *reinterpret_cast<const f4*>(Gr + ((i * RT + kt) * 64 + (on_blk ? src : lane)) * 4);
+          const f4 v = at_u32(reinterpret_cast<const f4*>(Gr), (i * RT + kt) * 64 + (on_blk ? src : lane));
           S.gv[i][kt] = on_blk ? v : f4{0.f, 0.f, 0.f, 0.f};
         }
       }
       S.g1[i] = *reinterpret_cast<const f4*>(Go + NMAT + 16 * i + 4 * ((lane >> 4) - (D / 2) * c_out));
     }
   };
-  auto step = [&](int t, const Step& S, Step& next) {
+  auto step = [&](int i, const Step& S, Step& next) {
+    const int t = S.t;
     const float2 q1 = S.q1, q2 = S.q2;
     const float th2 = S.th2;
     // unconditional (the last step re-reads its own time) so that the waits
     // for this step's operands never cover the loads just issued
-    load_step(next, min(t + 1, tr.y));
+    load_step(next, min(i + 1, mine - 1));
     float av[W], bv[SPLIT ? 1 : W];
     uint32_t bh[SPLIT ? W / 2 : 1], bl[SPLIT ? W / 2 : 1];
     float bm[NCH], zax[NCH];
@@ -1085,58 +1185,53 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
       }
     }
   };
-  Step sa, sb;
-  load_step(sa, tr.x);
-  for (int t = tr.x; t <= tr.y; t += 2) {
-    step(t, sa, sb);
-    if (t + 1 > tr.y) break;
-    step(t + 1, sb, sa);
+  if (mine > 0) {   // uniform over the wave
+    Step sa, sb;
+    load_step(sa, 0);
+    for (int i = 0; i < mine; i += 2) {
+      step(i, sa, sb);
+      if (i + 1 >= mine) break;
+      step(i + 1, sb, sa);
+    }
   }
-  const int own = lane >> 4;   // this lane's pixel is column lane & 15 of group lane >> 4
-  if constexpr (NCH == 1) {
-    // the four row groups of each pixel sit in lanes l, l ^ 16, l ^ 32, l ^ 48
+  // The partial sums of each pixel sit in the lanes of its four row groups (two
+  // per channel for NCH = 2) of every wave that shares the item, the beta-axis
+  // terms in its own lane: all go to LDS, and the last wave (the one with the
+  // fewest times) adds them for its lane's pixel in a fixed order.
+  wave_sync();
+  float2* pz = reinterpret_cast<float2*>(As);   // [4][64] by pixel group and lane, then [NCH][64]
 #pragma unroll
-    for (int pg = 0; pg < 4; ++pg) {
-      pz_i[pg] = sum_xor32(sum_xor16(pz_i[pg]));
-      pz_f[pg] = sum_xor32(sum_xor16(pz_f[pg]));
-    }
-    acc_i[0] += own == 0 ? pz_i[0] : own == 1 ? pz_i[1] : own == 2 ? pz_i[2] : pz_i[3];
-    acc_f[0] += own == 0 ? pz_f[0] : own == 1 ? pz_f[1] : own == 2 ? pz_f[2] : pz_f[3];
+  for (int pg = 0; pg < 4; ++pg) pz[64 * pg + lane] = make_float2(pz_i[pg], pz_f[pg]);
+#pragma unroll
+  for (int c = 0; c < NCH; ++c) pz[64 * (4 + c) + lane] = make_float2(acc_i[c], acc_f[c]);
+  if (shared) {
+    __syncthreads();
+    if (wv != NW - 1) return;
   } else {
-    // channel c's two row groups sit in lanes 32 c + (l & 15) + {0, 16}: add
-    // them, then every lane fetches each channel's total for its own pixel
-#pragma unroll
-    for (int pg = 0; pg < 4; ++pg) {
-      pz_i[pg] = sum_xor16(pz_i[pg]);
-      pz_f[pg] = sum_xor16(pz_f[pg]);
-    }
-#pragma unroll
-    for (int c = 0; c < NCH; ++c) {
-      const int from = 32 * c + (lane & 15);
-#pragma unroll
-      for (int pg = 0; pg < 4; ++pg) {
-        const float vi = __shfl(pz_i[pg], from), vf = __shfl(pz_f[pg], from);
-        if (pg == own) {
-          acc_i[c] += vi;
-          acc_f[c] += vf;
-        }
-      }
-    }
+    wave_sync();
   }
 #pragma unroll
   for (int c = 0; c < NCH; ++c) {
     if (NCH * fgrp + c >= nf) break;   // uniform over the wave
-    if (args.dfull != nullptr) {        // uniform over the wave
-      if (k < args.nv)
-        args.dfull[static_cast<size_t>(args.voff[k]) + static_cast<size_t>(fch[c]) * args.fstride] =
-            d_omega * acc_i[c];
-    } else {
-      dimg[static_cast<size_t>(fch[c]) * nvp + k] = d_omega * acc_i[c];
+    float si = 0.f, sf = 0.f;
+    for (int w = shared ? 0 : wv; w <= wv; ++w) {
+      const float2* x = reinterpret_cast<const float2*>(As_all[w]);
+      float2 v = x[64 * (4 + c) + lane];
+#pragma unroll
+      for (int g = c * (4 / NCH); g < (c + 1) * (4 / NCH); ++g) {
+        const float2 z = x[64 * (lane >> 4) + 16 * g + (lane & 15)];
+        v.x += z.x;
+        v.y += z.y;
+      }
+      si += v.x;
+      sf += v.y;
     }
-    float pf = acc_f[c] * ival[c];
+    put(chunk, fch[c], d_omega * si);
+    float pf = sf * img[static_cast<size_t>(fch[c]) * nvp + k];
 #pragma unroll
     for (int o = 32; o >= 1; o >>= 1) pf += __shfl_xor(pf, o);
-    if (lane == 0) f_part[static_cast<size_t>(fch[c]) * nchunks + chunk] = d_omega * kappa[c] * pf;
+    const float sig = fw * args.sigr[fch[c]], kappa = 1.0f / (sig * sig * fw);   // dB/dF = B theta^2 kappa
+    if (lane == 0) f_part[static_cast<size_t>(fch[c]) * nchunks + chunk] = d_omega * kappa * pf;
   }
 }
 
@@ -1154,7 +1249,7 @@ static void fwd_d(const vis_field* f, const float* img, const float* fwhm, float
   }
   ProfScope ps(&f->prof, "k_fringe_fwd", st);
   const FwdArgs a{f->n_freq, f->n_time, f->nv_pad, f->n_ubl, static_cast<float>(f->d_omega),
-                  T.dnu, T.sigr, T.q1, T.q2, T.th2, T.tchunk_off, T.tchunk, T.ubl_nm,
+                  T.dnu, T.sigr, T.q1, T.q2, T.th2, T.tchunk_off, T.tchunk, T.tchunk_ex, T.ubl_nm,
                   img, fwhm, vu, split ? f->scr.fscale : nullptr};
   if (split)
     launch_k<KFringeFwd<D, true>>(dim3(nblk), 0, a, st, "k_fringe_fwd");
@@ -1166,14 +1261,17 @@ template <int D>
 static void adj_d(const vis_field* f, const float* img, const float* fwhm, const float* gco,
                   float* dimg, float* dfull, float* f_part, hipStream_t st) {
   constexpr int nch = adj_channels_per_tile(D);
-  const int nblk = static_cast<int>(round_up(static_cast<long>((f->n_freq + nch - 1) / nch) * f->n_chunks, 8));
+  const int nfg = (f->n_freq + nch - 1) / nch;
+  const int nblk = static_cast<int>(round_up(static_cast<long>(nfg) * f->n_chunks, 8));
+  const int split_chunks = kAdjRounds * f->n_cu * (D <= 8 ? 16 : 8) / nfg;   // resident waves per CU
   const auto& T = f->tab;
   ProfScope ps(&f->prof, "k_fringe_adj", st);
   BV_REQUIRE(f->dtile == D, VIS_EINVAL, "internal: adjoint tile mismatch");
   BV_REQUIRE((dimg == nullptr) != (dfull == nullptr), VIS_EINVAL, "internal: one adjoint output");
   const AdjArgs a{f->n_freq, f->n_time, f->nv_pad, f->n_chunks, f->gstride,
                   static_cast<float>(f->d_omega), T.dnu, T.sigr, T.q1, T.q2, T.th2,
-                  T.chunk_t, img, fwhm, gco, gco, dimg, f_part, dfull, T.sep_voff, f->nv,
+                  T.chunk_ex, f->sigr_max, split_chunks,
+                  static_cast<unsigned>(((1ull << 32) + nfg - 1) / nfg), T.ctime_off, T.ctime, T.ctime_ex, img, fwhm, gco, gco, dimg, f_part, dfull, T.sep_voff, f->nv,
                   f->basis->nphi_b};
   if (fringe_split(f))
     launch_k<KFringeAdj<D, true>>(dim3(nblk), 0, a, st, "k_fringe_adj");

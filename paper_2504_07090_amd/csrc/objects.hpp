@@ -103,7 +103,13 @@ struct FieldTables {
   float* th2 = nullptr;            // [n_time][nv_pad] zenith angle^2, kBelowHorizon if U <= 0
   int2* chunk_t = nullptr;         // [n_chunks] first / last time the chunk is visible
   int* tchunk_off = nullptr;       // [n_time + 1] CSR of chunks active at each time
-  int* tchunk = nullptr;           // [sum] chunk indices
+  int* tchunk = nullptr;           // [sum] chunk indices, ascending tchunk_ex per time
+  float* tchunk_ex = nullptr;      // [sum] theta^2 of the chunk's nearest pixel above the horizon
+                                   //   minus that of the nearest pixel of the sky, at that time
+  int* ctime_off = nullptr;        // [n_chunks + 1] CSR of the times at which each chunk is active
+  int* ctime = nullptr;            // [sum] time indices, ascending ctime_ex per chunk
+  float* ctime_ex = nullptr;       // [sum] the same excess
+  float* chunk_ex = nullptr;       // [n_chunks] each chunk's smallest excess, ascending
   int2* bl_ant = nullptr;          // [n_bl] (i, j)
   int* bl_u = nullptr;             // [n_bl] unique index, negative-encoded sign: u or ~u
   int4* bl_pos = nullptr;          // [n_bl] position of baseline k in u_list, and of its
@@ -143,6 +149,7 @@ struct vis_field {
   int sep_nkb = 0;                 // separable fields: entries of tab.sep_kb
   double d_omega = 0.0;
   double beam_ref_hz = 150e6;
+  float sigr_max = 0.f;            // largest tab.sigr: the widest beam of the field
   double fwd_macs = 0.0;
   bv::FieldTables tab;
   bv::FieldScratch scr;
