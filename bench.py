@@ -58,7 +58,7 @@ EPS = 0.02   # leapfrog step in units of the diagonal-Hessian scale
 # reported only while the kernel sources and build flags hash to the value it
 # was taken with.
 TRAFFIC = {
-    "sources": ["paper_2504_07090_amd/csrc/fringe.hip", "paper_2504_07090_amd/csrc/common.hpp",
+    "sources": ["paper_2504_07090_amd/csrc/fringe.hpp", "paper_2504_07090_amd/csrc/common.hpp",
                 "paper_2504_07090_amd/build.py"],
     "sha256": "4a70a4f9bdfaf8239f323f3e473f87d5a2f626af547bdf4b32b4be21f49b12d5",
     "bytes_per_launch": {"k_fringe_adj": 195683636, "k_fringe_fwd": 235222678},

@@ -19,7 +19,7 @@ void check_field(const vis_field* f) {
 namespace bv {
 
 void forward_core(const vis_field* f, const float* alm, const float* fwhm, hipStream_t s) {
-  { StageScope sc(kStageSynthFwd); launch_synth_fwd(f, alm, f->scr.img, s); }
+  { StageScope sc(kStageSynthFwd); launch_synth_fwd(f, alm, fwhm, f->scr.img, s); }
   { StageScope sc(kStageFringeFwd); launch_fringe_fwd(f, f->scr.img, fwhm, f->scr.vu, s); }
 }
 
@@ -42,7 +42,7 @@ void adjoint_tail(const vis_field* f, const float* fwhm, float* grad_alm, float2
   }
   if (grad_alm != nullptr) {
     StageScope sc(kStageSynthAdj);
-    launch_synth_adj(f, full ? nullptr : f->scr.dimg, grad_alm, s);
+    launch_synth_adj(f, full ? nullptr : f->scr.dimg, fwhm, grad_alm, s);
   }
 }
 

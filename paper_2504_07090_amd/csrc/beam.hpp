@@ -1,0 +1,49 @@
+// Beam cut of the evaluation kernels (kBeamBits): every kernel of a field
+// derives the same cut from the beam width on the device, so that what one
+// leaves out no other reads.
+#pragma once
+
+#include "common.hpp"
+
+namespace bv {
+
+// Excess theta^2 beyond which a beam of width sig is cut.
+__device__ __forceinline__ float beam_cut(float sig) {
+  return kBeamBits * 2.0f * static_cast<float>(kLn2) * sig * sig;
+}
+
+// Number of leading entries of an ascending excess list up to `cut`; the same
+// in every lane.  SEG 64-entry segments load at once.  An undefined cut (NaN)
+// cuts nothing.
+template <int SEG>
+__device__ __forceinline__ int beam_prefix(const float* __restrict__ ex, int n, float cut, int lane) {
+  int cnt = 0;
+  for (int base = 0; base < n; base += 64 * SEG) {
+    float e[SEG];
+#pragma unroll
+    for (int q = 0; q < SEG; ++q) e[q] = ex[min(base + 64 * q + lane, n - 1)];
+    int c = 0;
+#pragma unroll
+    for (int q = 0; q < SEG; ++q)
+      c += __popcll(__ballot(base + 64 * q + lane < n && !(e[q] > cut)));
+    cnt += c;
+    if (c < 64 * SEG) break;
+  }
+  return cnt;
+}
+
+// First and last entry up to `cut` of an excess list in any order ((n, -1) if
+// there is none); the same in every lane.
+__device__ __forceinline__ int2 beam_range(const float* __restrict__ ex, int n, float cut, int lane) {
+  int2 r = make_int2(n, -1);
+  for (int base = 0; base < n; base += 64) {
+    const float e = ex[min(base + lane, n - 1)];
+    const unsigned long long in = __ballot(base + lane < n && !(e > cut));
+    if (in == 0) continue;
+    if (r.y < 0) r.x = base + __builtin_ctzll(in);
+    r.y = base + 63 - __builtin_clzll(in);
+  }
+  return r;
+}
+
+}  // namespace bv

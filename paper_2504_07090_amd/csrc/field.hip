@@ -498,11 +498,14 @@ static void carve_field(vis_field* f, Carver& cv, int n_tchunk) {
   if (!dense) {
     S.sep_g = cv.take<float>(static_cast<size_t>(f->basis->nz) * f->kaz * nfq);
     S.sep_dfull = cv.take<float>(static_cast<size_t>(f->basis->nz) * nfq * f->basis->nphi_b);
-    S.sep_at = cv.take<float>(static_cast<size_t>(f->n_modes) * nfq);
     T.sep_kb_off = cv.take<int>(f->basis->nz + 1);
     const size_t nkb_max = static_cast<size_t>(f->basis->nz) * ceil_div(f->basis->nphi, kSepStep);
     T.sep_kb = cv.take<int>(nkb_max);
-    T.sep_kb_ring = cv.take<int>(nkb_max);
+    T.sep_kb_ex = cv.take<float>(nkb_max);
+    T.sep_sorted = cv.take<int>(nkb_max);
+    T.sep_sorted_ex = cv.take<float>(nkb_max);
+    T.sep_ring_ex = cv.take<float>(f->basis->nz);
+    T.sep_ring = cv.take<int>(f->basis->nz);
     T.sep_voff = cv.take<int>(nvp);
   }
   if (f->precision != VIS_FP32) {
@@ -752,6 +755,13 @@ vis_status vis_field_create(const vis_basis* basis, const vis_field_desc* desc, 
       sigr[k] = static_cast<float>(desc->beam_ref_hz / freq[k] * kFwhmToSigma);
       f->sigr_max = std::max(f->sigr_max, sigr[k]);
     }
+    {
+      // |p| <= |e| / c for every direction, |y| <= 1/2
+      const double* e1 = desc->lattice_e1_m;
+      const double* e2 = desc->lattice_e2_m;
+      const double len = std::max(std::hypot(e1[0], e1[1]), std::hypot(e2[0], e2[1]));
+      f->max_turns = static_cast<float>(0.5 + 0.5 * (fmax - fmin) * len / kCLight);
+    }
     auto phase_table = [&](const std::vector<double>& p) {
       std::vector<float2> q(p.size());
       for (size_t i = 0; i < p.size(); ++i) {
@@ -793,7 +803,8 @@ vis_status vis_field_create(const vis_basis* basis, const vis_field_desc* desc, 
     for (int k = 0; k < f->nv; ++k) vidx[g.vpix[k]] = k;
     up(T.vidx, vidx, s);
     // named, like the tables above, until the stream is synchronised
-    std::vector<int> kb_off, kb, kb_ring, voff;
+    std::vector<int> kb_off, kb, kb_sorted, ring_order, voff;
+    std::vector<float> kb_ex, kb_sorted_ex, ring_ex;
     if (f->synthesis == VIS_SYNTH_SEPARABLE) {
       // rows of the Legendre stage beyond 2 lmax + 1 are never written: keep them zero
       BV_HIP(hipMemsetAsync(f->scr.sep_g, 0,
@@ -804,22 +815,42 @@ vis_status vis_field_create(const vis_basis* basis, const vis_field_desc* desc, 
                             sizeof(float) * basis->nz * f->n_freq * static_cast<size_t>(basis->nphi_b), s));
       // the column batches of each ring that the azimuthal stages visit
       kb_off.assign(1, 0);
+      std::vector<std::pair<float, int>> all, rings;
       for (int j = 0; j < basis->nz; ++j) {
+        std::vector<std::pair<float, int>> row;
         for (int k0 = 0; k0 < basis->nphi; k0 += kSepStep) {
-          bool any = false;
-          for (int k = k0; k < std::min(basis->nphi, k0 + kSepStep); ++k)
-            any = any || vidx[static_cast<size_t>(j) * basis->nphi + k] >= 0;
-          if (any) {
-            kb.push_back(k0);
-            kb_ring.push_back(j);
+          float ex = kBelowHorizon;
+          for (int k = k0; k < std::min(basis->nphi, k0 + kSepStep); ++k) {
+            const int slot = vidx[static_cast<size_t>(j) * basis->nphi + k];
+            if (slot >= 0) ex = std::min(ex, g.chunk_ex[slot / kChunk]);
           }
+          if (ex < kBelowHorizon) row.emplace_back(ex, k0);
+        }
+        std::sort(row.begin(), row.end());
+        rings.emplace_back(row.empty() ? kBelowHorizon : row[0].first, j);
+        for (const auto& r : row) {
+          kb.push_back(r.second);
+          kb_ex.push_back(r.first);
+          all.emplace_back(r.first, j * basis->nphi + r.second);
         }
         kb_off.push_back(static_cast<int>(kb.size()));
+      }
+      for (const auto& r : rings) ring_ex.push_back(r.first);
+      std::sort(rings.begin(), rings.end());
+      std::sort(all.begin(), all.end());
+      for (const auto& r : rings) ring_order.push_back(r.second);
+      for (const auto& r : all) {
+        kb_sorted.push_back(r.second);
+        kb_sorted_ex.push_back(r.first);
       }
       f->sep_nkb = static_cast<int>(kb.size());
       up(T.sep_kb_off, kb_off, s);
       up(T.sep_kb, kb, s);
-      up(T.sep_kb_ring, kb_ring, s);
+      up(T.sep_kb_ex, kb_ex, s);
+      up(T.sep_sorted, kb_sorted, s);
+      up(T.sep_sorted_ex, kb_sorted_ex, s);
+      up(T.sep_ring_ex, ring_ex, s);
+      up(T.sep_ring, ring_order, s);
       BV_REQUIRE(static_cast<double>(basis->nz) * f->n_freq * basis->nphi_b < 2147483647.0, VIS_EINVAL,
                  "separable dL/dI rows of %d x %d x %d floats exceed 32-bit offsets", basis->nz, f->n_freq,
                  basis->nphi_b);

@@ -33,7 +33,10 @@
 // with G built from omega(n, +m), omega(n, -m); it runs as the GEMM
 // T[r][p] = sum_c G[r][c] Bb[c][p] on MFMA followed by a per-pixel dot with A.
 // dL/dI(p, nu) = dOmega sum_t B Z and dL/dF = dOmega sum (dB/dF) I Z follow.
+#pragma once
+
 #include "batch.hpp"
+#include "beam.hpp"
 #include "objects.hpp"
 
 namespace bv {
@@ -50,13 +53,11 @@ __device__ __forceinline__ void wave_sync() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
-// sin and cos of 2 pi x for |x| <= 1/2.  The argument is already reduced to
-// one turn in FP64, so the hardware transcendental units (which take their
-// argument in turns) are used directly; BV_ACCURATE_TRIG selects the
-// correctly-rounded library routine instead.
+// sin and cos of 2 pi x on the hardware units, which take their argument in
+// turns; BV_ACCURATE_TRIG selects the correctly-rounded library routine instead.
 __device__ __forceinline__ void sincos_rev(float x, float& s, float& c) {
 #ifdef BV_ACCURATE_TRIG
-  sincospif(2.0f * x, &s, &c);
+  sincospif(2.0f * (x - __builtin_rintf(x)), &s, &c);
 #else
   s = __builtin_amdgcn_sinf(x);
   c = __builtin_amdgcn_cosf(x);
@@ -77,38 +78,41 @@ __device__ __forceinline__ V at_u32(const V* base, int k) {
                                      static_cast<uint32_t>(k) * static_cast<uint32_t>(sizeof(V)));
 }
 
-// Reduced phase of nu_f p in cycles, in [-1/2, 1/2], in FP32 from the
-// table entry q = (y, p), y = nu_c p reduced modulo 1 on the host in FP64,
-// and dnu = nu_f - nu_c: x = y + dnu p is at most a few cycles, so one fma
-// and one round-to-integer keep the error near one FP32 rounding of x.
-__device__ __forceinline__ float reduced_cycles(float dnu, float2 q) {
-  const float x = __builtin_fmaf(dnu, q.y, q.x);
-  return x - __builtin_rintf(x);
-}
-
-// Excess theta^2 beyond which a beam of width sig is cut (kBeamBits).
-__device__ __forceinline__ float beam_cut(float sig) {
-  return kBeamBits * 2.0f * static_cast<float>(kLn2) * sig * sig;
-}
-
-// Number of leading entries of an ascending excess list up to `cut`; the same
-// in every lane.  SEG 64-entry segments load at once.  An undefined cut (NaN)
-// cuts nothing.
-template <int SEG>
-__device__ __forceinline__ int beam_prefix(const float* __restrict__ ex, int n, float cut, int lane) {
-  int cnt = 0;
-  for (int base = 0; base < n; base += 64 * SEG) {
-    float e[SEG];
-#pragma unroll
-    for (int q = 0; q < SEG; ++q) e[q] = ex[min(base + 64 * q + lane, n - 1)];
-    int c = 0;
-#pragma unroll
-    for (int q = 0; q < SEG; ++q)
-      c += __popcll(__ballot(base + 64 * q + lane < n && !(e[q] > cut)));
-    cnt += c;
-    if (c < 64 * SEG) break;
+// A lane's elements of (uniform) rows in a loop over rows.  ROW: the byte
+// offsets look changed in every iteration (`touch` issues no instruction), so
+// that the row's address is formed on the scalar unit; otherwise the optimizer
+// adds the lane to the array's base once, outside, and pays a 64-bit vector add
+// per load.  The vector adds cost more than the scalar ones where the vector
+// unit is the shorter chain (extents up to 6: 8 of 57 vector instructions per
+// chunk of a 37-dish forward pass, 205 -> 196 us; the adjoint 210 -> 207 us),
+// less above (91 dishes, adjoint 334 us against 339 us with ROW).
+template <bool ROW>
+struct LaneOffset {
+  uint32_t o4, o8;
+  __device__ explicit LaneOffset(int lane) : o4(4u * lane), o8(8u * lane) {}
+  __device__ __forceinline__ void touch(int row) {
+    if constexpr (ROW) asm("" : "+v"(o4), "+v"(o8) : "s"(row));
   }
-  return cnt;
+  __device__ __forceinline__ float at(const float* row) const {
+    return *reinterpret_cast<const float*>(reinterpret_cast<const char*>(row) + o4);
+  }
+  __device__ __forceinline__ float2 at(const float2* row) const {
+    return *reinterpret_cast<const float2*>(reinterpret_cast<const char*>(row) + o8);
+  }
+};
+
+// Phase of nu_f p in cycles, modulo whole cycles, in FP32 from the table entry
+// q = (y, p), y = nu_c p reduced modulo 1 on the host in FP64, and dnu = nu_f -
+// nu_c: x = y + dnu p, one fma.  The hardware sine and cosine take an argument
+// of up to 256 turns and reduce it exactly (errors on [-2, 2] as on [-1/2,
+// 1/2], measured), so only fields whose |dnu p| may exceed kMaxTurns (WRAP: a
+// lattice step of a kilometre over a half band of 75 MHz) reduce it here; the
+// two instructions per axis cost 3% of both passes.
+constexpr float kMaxTurns = 240.0f;
+template <bool WRAP>
+__device__ __forceinline__ float phase_cycles(float dnu, float2 q) {
+  const float x = __builtin_fmaf(dnu, q.y, q.x);
+  return WRAP ? x - __builtin_rintf(x) : x;
 }
 
 // Block index -> logical index so that consecutive logical indices share an
@@ -375,7 +379,10 @@ __device__ __forceinline__ h8 tr_operand(const uint32_t* base, int pix0, int til
 // scale = 2^(13 - e) with dOmega max |I| < 2^e (B <= 1), so that every
 // |dOmega B I scale| < 2^13 and its FP16 lo part stays a normal number.
 struct ChanScaleArgs {
-  int nvp;
+  int nvp, nchunks;
+  float sigr_max;
+  const float* chunk_ex;
+  const float* fwhm;
   const float* img;
   float* part;   // [n_freq][kScaleParts]
 };
@@ -385,8 +392,11 @@ struct KChanScale {
   static constexpr int kThreads = 256, kWaves = 1;
   static __device__ void run(const ChanScaleArgs& a, const Blk& B) {
     __shared__ float red[4];
-    const int seg = (a.nvp + kScaleParts - 1) / kScaleParts;
-    const int k0 = B.y * seg, k1 = min(a.nvp, k0 + seg);
+    // the slots the forward pass visits (the sky elsewhere is not current)
+    const int ns = kChunk * beam_prefix<8>(a.chunk_ex, a.nchunks, beam_cut(a.fwhm[0] * a.sigr_max),
+                                           threadIdx.x & 63);
+    const int seg = (ns + kScaleParts - 1) / kScaleParts;
+    const int k0 = B.y * seg, k1 = min(ns, k0 + seg);
     const float* row = a.img + static_cast<size_t>(B.x) * a.nvp;
     float m = 0.f;
     for (int k = k0 + threadIdx.x; k < k1; k += 256) m = fmaxf(m, fabsf(row[k]));
@@ -468,15 +478,15 @@ __host__ __device__ constexpr bool fwd_axis_in_tile(int D) {
 // SPLIT: the P tile runs on FP16 MFMA (K = 32) as three products of hi + lo
 // pairs, A_hi B_hi + A_lo B_hi + A_hi B_lo, accumulated in FP32; the beam-
 // weighted sky carries the channel's power-of-two scale, undone at the end.
-template <int D, bool SPLIT = false>
+template <int D, bool SPLIT, bool WRAP>
 struct KFringeFwd {
   using Args = FwdArgs;
   static constexpr int kThreads = 64 * kFwdWaves, kWaves = D <= 8 ? 4 : 2;
   static __device__ void run(const FwdArgs& args, const Blk& B);
 };
 
-template <int D, bool SPLIT>
-__device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
+template <int D, bool SPLIT, bool WRAP>
+__device__ void KFringeFwd<D, SPLIT, WRAP>::run(const FwdArgs& args, const Blk& B) {
   const int nf = args.nf, nt = args.nt, nvp = args.nvp, nubl = args.nubl;
   const float d_omega = args.d_omega;
   const float2* Q1 = args.Q1;
@@ -554,14 +564,38 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
   const float* tht = TH2 + static_cast<size_t>(t) * nvp;
 
   struct G { float2 q1, q2; float th, iv[NCH]; };
-  auto load = [&](int ci) {
-    const int k = tchunk[cbeg + cend - 1 - ci] * kChunk + lane;
+  // this wave's chunks: entry j is the list's (wv + kFwdWaves j)-th from its end
+  constexpr int S = kFwdWaves;
+  constexpr bool ROW = D <= 6;   // scalar row addresses (LaneOffset) and chunk indices
+  const int mine = max(0, (cend - cbeg - wv + S - 1) / S);
+  auto chunk_at = [&](int j) {   // uniform
+#if defined(__HIP_DEVICE_COMPILE__)
+    if constexpr (ROW) {   // through the constant address space: a scalar load
+      typedef const int __attribute__((address_space(4))) ConstInt;
+      return ((const ConstInt*)(reinterpret_cast<uintptr_t>(tchunk)))[cend - 1 - wv - S * j];
+    }
+#endif
+    return tchunk[cend - 1 - wv - S * j];
+  };
+  LaneOffset<ROW> lo(lane);
+  auto load = [&](int chunk) {
     G g;
-    g.q1 = at_u32(q1t, k);
-    g.q2 = at_u32(q2t, k);
-    g.th = at_u32(tht, k);
+    if constexpr (ROW) {
+      const int k0 = chunk * kChunk;
+      lo.touch(k0);
+      g.q1 = lo.at(q1t + k0);
+      g.q2 = lo.at(q2t + k0);
+      g.th = lo.at(tht + k0);
 #pragma unroll
-    for (int c = 0; c < NCH; ++c) g.iv[c] = at_u32(imf[c], k);
+      for (int c = 0; c < NCH; ++c) g.iv[c] = lo.at(imf[c] + k0);
+    } else {
+      const int k = chunk * kChunk + lane;
+      g.q1 = at_u32(q1t, k);
+      g.q2 = at_u32(q2t, k);
+      g.th = at_u32(tht, k);
+#pragma unroll
+      for (int c = 0; c < NCH; ++c) g.iv[c] = at_u32(imf[c], k);
+    }
     return g;
   };
   // powers of one chunk into LDS, channel c in rows and columns 2D c ..
@@ -571,8 +605,8 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
     float wlast = 0.f;   // the weight (times its scale) of the last channel
 #pragma unroll
     for (int c = 0; c < NCH; ++c) {
-      const float x1 = reduced_cycles(dnu[c], g.q1);
-      const float x2 = reduced_cycles(dnu[c], g.q2);
+      const float x1 = phase_cycles<WRAP>(dnu[c], g.q1);
+      const float x2 = phase_cycles<WRAP>(dnu[c], g.q2);
       const float s = chan_on[c] * d_omega * beam_exp2(-g.th * kb[c]) * g.iv[c];
       float s1, c1, s2, c2;
       sincos_rev(x1, s1, c1);
@@ -668,13 +702,19 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
             acc[q % NACC][i][j] = mfma4(a[q][i], b[q][j], acc[q % NACC][i][j]);
     }
   };
-  // one chunk but the wave's last: the MFMAs of chunk ci (register operands)
-  // interleaved with the generation of the wave's next chunk from `cur`, while
-  // the geometry of the one after it loads into `nxt`; the loop below is
-  // unrolled by two so the two geometry sets swap roles without register copies
-  constexpr int S = kFwdWaves;   // chunk stride of one wave
-  auto chunk_step = [&](int ci, const G& cur, G& nxt) {
-    nxt = load(min(ci + 2 * S, cend - 1));
+  // one chunk but the wave's last: the MFMAs of chunk j (register operands)
+  // interleaved with the generation of the next chunk from `cur`, while the
+  // geometry of the one after it loads into `nxt` (ROW: its chunk `ahead` was
+  // read a step earlier); the loop below is unrolled by two so the two geometry
+  // sets swap roles without register copies
+  int ahead = 0;
+  auto chunk_step = [&](int j, const G& cur, G& nxt) {
+    if constexpr (ROW) {
+      nxt = load(ahead);
+      ahead = chunk_at(min(j + 3, mine - 1));
+    } else {
+      nxt = load(chunk_at(min(j + 2, mine - 1)));
+    }
     // keep the prefetch here: the sources are read-only, so the optimizer
     // would otherwise re-issue the loads right before their use
     asm volatile("" ::: "memory");
@@ -699,22 +739,22 @@ __device__ void KFringeFwd<D, SPLIT>::run(const FwdArgs& args, const Blk& B) {
     operands();
     wave_sync();
   };
-  const int c0 = cbeg + wv;
-  if (c0 < cend) {   // uniform over the wave
-    generate(load(c0));
-    G ga = load(min(c0 + S, cend - 1)), gb;
+  if (mine > 0) {   // uniform over the wave
+    ahead = chunk_at(min(2, mine - 1));
+    generate(load(chunk_at(0)));
+    G ga = load(chunk_at(min(1, mine - 1))), gb;
     wave_sync();
     operands();
     wave_sync();
-    int ci = c0;
-    if (((cend - 1 - c0) / S) & 1) {   // an odd number of steps before the last chunk
-      chunk_step(ci, ga, gb);
+    int j = 0;
+    if ((mine - 1) & 1) {   // an odd number of steps before the last chunk
+      chunk_step(j, ga, gb);
       ga = gb;
-      ci += S;
+      ++j;
     }
-    for (; ci + S < cend; ci += 2 * S) {
-      chunk_step(ci, ga, gb);
-      chunk_step(ci + S, gb, ga);
+    for (; j + 1 < mine; j += 2) {
+      chunk_step(j, ga, gb);
+      chunk_step(j + 1, gb, ga);
     }
     products();
   }
@@ -885,15 +925,15 @@ struct AdjArgs {
 __host__ __device__ constexpr int adj_waves(int D) { return D <= 8 ? 4 : 2; }
 constexpr int kAdjRounds = 3;
 
-template <int D, bool SPLIT>
+template <int D, bool SPLIT, bool WRAP>
 struct KFringeAdj {
   using Args = AdjArgs;
   static constexpr int kThreads = 64 * adj_waves(D), kWaves = 1;
   static __device__ void run(const AdjArgs& args, const Blk& B);
 };
 
-template <int D, bool SPLIT>
-__device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
+template <int D, bool SPLIT, bool WRAP>
+__device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& B) {
   const int nf = args.nf, nvp = args.nvp, nchunks = args.nchunks, gstride = args.gstride;
   const float d_omega = args.d_omega;
   const float2* Q1 = args.Q1;
@@ -1029,13 +1069,15 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
     }
     return __builtin_amdgcn_readlane(tl, e & 63);
   };
+  LaneOffset<(D <= 6)> lo(lane);
   auto load_step = [&](Step& S, int i) {
     const int t = time_at(i);
+    lo.touch(t);
     S.t = t;
-    const size_t row = static_cast<size_t>(t) * nvp;   // uniform over the wave
-    S.q1 = at_u32(Q1 + row, k);
-    S.q2 = at_u32(Q2 + row, k);
-    S.th2 = at_u32(TH2 + row, k);
+    const size_t row = static_cast<size_t>(t) * nvp + chunk * kChunk;   // uniform over the wave
+    S.q1 = lo.at(Q1 + row);
+    S.q2 = lo.at(Q2 + row);
+    S.th2 = lo.at(TH2 + row);
     const size_t tbase = static_cast<size_t>(t) * gst;
     // the coefficient operand: this lane's row channel's slice; zero off the
     // diagonal blocks and for a channel past the band
@@ -1077,8 +1119,8 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
     for (int c = 0; c < NCH; ++c) {
       const float* G = gco_at(t, c);
       bm[c] = beam_exp2(-th2 * kb[c]);
-      const float x1 = reduced_cycles(dnu[c], q1);
-      const float x2 = reduced_cycles(dnu[c], q2);
+      const float x1 = phase_cycles<WRAP>(dnu[c], q1);
+      const float x2 = phase_cycles<WRAP>(dnu[c], q2);
       float s1, c1, s2, c2;
       sincos_rev(x1, s1, c1);
       sincos_rev(x2, s2, c2);
@@ -1236,6 +1278,11 @@ __device__ void KFringeAdj<D, SPLIT>::run(const AdjArgs& args, const Blk& B) {
 }
 
 // ------------------------------------------------------------ launchers --
+template <class K>
+struct KernelTag {
+  using Kernel = K;
+};
+
 template <int D>
 static void fwd_d(const vis_field* f, const float* img, const float* fwhm, float2* vu, hipStream_t st) {
   constexpr int nch = fwd_channels_per_tile(D);
@@ -1245,16 +1292,18 @@ static void fwd_d(const vis_field* f, const float* img, const float* fwhm, float
   if (split) {
     ProfScope ps(&f->prof, "k_chan_scale", st);
     launch_k<KChanScale>(dim3(f->n_freq, kScaleParts), 0,
-                         ChanScaleArgs{f->nv_pad, img, f->scr.fscale}, st, "k_chan_scale");
+                         ChanScaleArgs{f->nv_pad, f->n_chunks, f->sigr_max, T.chunk_ex, fwhm, img, f->scr.fscale}, st, "k_chan_scale");
   }
   ProfScope ps(&f->prof, "k_fringe_fwd", st);
   const FwdArgs a{f->n_freq, f->n_time, f->nv_pad, f->n_ubl, static_cast<float>(f->d_omega),
                   T.dnu, T.sigr, T.q1, T.q2, T.th2, T.tchunk_off, T.tchunk, T.tchunk_ex, T.ubl_nm,
                   img, fwhm, vu, split ? f->scr.fscale : nullptr};
+  const bool wrap = f->max_turns > kMaxTurns;
+  auto launch = [&](auto k) { launch_k<typename decltype(k)::Kernel>(dim3(nblk), 0, a, st, "k_fringe_fwd"); };
   if (split)
-    launch_k<KFringeFwd<D, true>>(dim3(nblk), 0, a, st, "k_fringe_fwd");
+    wrap ? launch(KernelTag<KFringeFwd<D, true, true>>{}) : launch(KernelTag<KFringeFwd<D, true, false>>{});
   else
-    launch_k<KFringeFwd<D, false>>(dim3(nblk), 0, a, st, "k_fringe_fwd");
+    wrap ? launch(KernelTag<KFringeFwd<D, false, true>>{}) : launch(KernelTag<KFringeFwd<D, false, false>>{});
 }
 
 template <int D>
@@ -1273,10 +1322,12 @@ static void adj_d(const vis_field* f, const float* img, const float* fwhm, const
                   T.chunk_ex, f->sigr_max, split_chunks,
                   static_cast<unsigned>(((1ull << 32) + nfg - 1) / nfg), T.ctime_off, T.ctime, T.ctime_ex, img, fwhm, gco, gco, dimg, f_part, dfull, T.sep_voff, f->nv,
                   f->basis->nphi_b};
+  const bool wrap = f->max_turns > kMaxTurns;
+  auto launch = [&](auto k) { launch_k<typename decltype(k)::Kernel>(dim3(nblk), 0, a, st, "k_fringe_adj"); };
   if (fringe_split(f))
-    launch_k<KFringeAdj<D, true>>(dim3(nblk), 0, a, st, "k_fringe_adj");
+    wrap ? launch(KernelTag<KFringeAdj<D, true, true>>{}) : launch(KernelTag<KFringeAdj<D, true, false>>{});
   else
-    launch_k<KFringeAdj<D, false>>(dim3(nblk), 0, a, st, "k_fringe_adj");
+    wrap ? launch(KernelTag<KFringeAdj<D, false, true>>{}) : launch(KernelTag<KFringeAdj<D, false, false>>{});
 }
 
 #define BV_DISPATCH_EXTENT(ext, CALL)          \
@@ -1289,23 +1340,5 @@ static void adj_d(const vis_field* f, const float* img, const float* fwhm, const
     else if (e_ <= 12) { CALL(12); }           \
     else { CALL(16); }                         \
   } while (0)
-
-void launch_fringe_fwd(const vis_field* f, const float* img, const float* fwhm, float2* vu,
-                       hipStream_t st) {
-#define BV_CALL_FWD(DD) fwd_d<DD>(f, img, fwhm, vu, st)
-  BV_DISPATCH_EXTENT(f->extent, BV_CALL_FWD);
-#undef BV_CALL_FWD
-}
-
-int fringe_tile_extent(int e) {
-  return e <= 2 ? 2 : e <= 4 ? 4 : e <= 6 ? 6 : e <= 8 ? 8 : e <= 12 ? 12 : 16;
-}
-
-void launch_fringe_adj(const vis_field* f, const float* img, const float* fwhm, const float* gco,
-                       float* dimg, float* f_part, hipStream_t st, float* dfull) {
-#define BV_CALL_ADJ(DD) adj_d<DD>(f, img, fwhm, gco, dimg, dfull, f_part, st)
-  BV_DISPATCH_EXTENT(f->extent, BV_CALL_ADJ);
-#undef BV_CALL_ADJ
-}
 
 }  // namespace bv

@@ -81,7 +81,6 @@ struct FieldScratch {
                                    //   (forward) or azimuthal stage output (adjoint)
   float* sep_dfull = nullptr;      // separable fields: [nz][n_freq][nphi_b] dL/dI on the full grid
                                    //   (zero at pixels never above the horizon and beyond nphi)
-  float* sep_at = nullptr;         // separable fields: [n_modes][n_freq] sky coefficients transposed
   float2* vu = nullptr;            // [n_time][n_freq][n_ubl] gain-free unique visibilities
   float* gco = nullptr;            // [n_time][n_freq][gstride] adjoint coefficients, MFMA layout
   double* chi_part = nullptr;      // [n_time * n_freq]
@@ -121,11 +120,17 @@ struct FieldTables {
   int2* ubl_nm = nullptr;          // [n_ubl] lattice (n1, n2), canonical
   int* ulut = nullptr;             // [(D+1) * (2D+1)] unique index of (n1, n2) or -1
   int4* cplan = nullptr;           // [gstride] source plan of each adjoint coefficient entry
-  // separable fields: per ring j, the first columns of the 32-column batches
-  // that hold a pixel above the horizon, sep_kb[sep_kb_off[j] .. sep_kb_off[j + 1])
-  int* sep_kb_off = nullptr;       // [nz + 1]
-  int* sep_kb = nullptr;           // [nz * ceil(nphi / 32)] at most
-  int* sep_kb_ring = nullptr;      // the ring of each sep_kb entry
+  // separable fields: the 32-column batches of the rings that hold a pixel
+  // above the horizon at some time, each with the smallest excess (chunk_ex) of
+  // the chunks its pixels belong to: a batch over the beam cut holds no pixel
+  // that the fringe passes visit
+  int* sep_kb_off = nullptr;       // [nz + 1] CSR: batches of ring j, ascending sep_kb_ex
+  int* sep_kb = nullptr;           // [nz * ceil(nphi / 32)] at most: first columns
+  float* sep_kb_ex = nullptr;      // the same length
+  int* sep_sorted = nullptr;       // [same] every batch as ring * nphi + first column, ascending excess
+  float* sep_sorted_ex = nullptr;
+  float* sep_ring_ex = nullptr;    // [nz] smallest excess of each ring (kBelowHorizon: none)
+  int* sep_ring = nullptr;         // [nz] the rings in ascending order of it
   int* sep_voff = nullptr;         // [nv_pad] offset of visible slot k's pixel in sep_dfull at
                                    //   channel 0: ring * n_freq * nphi_b + column
 };
@@ -150,6 +155,7 @@ struct vis_field {
   double d_omega = 0.0;
   double beam_ref_hz = 150e6;
   float sigr_max = 0.f;            // largest tab.sigr: the widest beam of the field
+  float max_turns = 0.f;           // bound on |y + dnu p| of the phase tables, cycles
   double fwd_macs = 0.0;
   bv::FieldTables tab;
   bv::FieldScratch scr;
@@ -159,10 +165,13 @@ struct vis_field {
 namespace bv {
 
 // ---- launchers (stream-ordered, no host sync) ----------------------------
-void launch_synth_fwd(const vis_field* f, const float* alm, float* img, hipStream_t st);
+// Only the slots of chunks within the beam of the field's widest channel are
+// written (forward) or read (adjoint): the fringe passes visit no others.
+void launch_synth_fwd(const vis_field* f, const float* alm, const float* fwhm, float* img, hipStream_t st);
 // Dense fields read dL/dI from dimg; separable fields take dimg == nullptr and
 // read it from the full-grid scratch, where the adjoint fringe pass put it.
-void launch_synth_adj(const vis_field* f, const float* dimg, float* grad_alm, hipStream_t st);
+void launch_synth_adj(const vis_field* f, const float* dimg, const float* fwhm, float* grad_alm,
+                      hipStream_t st);
 void launch_fringe_fwd(const vis_field* f, const float* img, const float* fwhm, float2* vu,
                        hipStream_t st);
 // dL/dI goes to dimg ([n_freq][nv_pad]) or, for separable fields, with

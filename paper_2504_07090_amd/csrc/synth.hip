@@ -357,12 +357,13 @@ __device__ void KReduceSplits::run(const ReduceSplitsArgs& args_, const Blk& B_)
 void launch_synth_fwd_split(const vis_field* f, const float* alm, float* dst, int nsplit, int kps,
                             hipStream_t st);
 void launch_synth_adj_split(const vis_field* f, const float* dimg, int kps, hipStream_t st);
-void launch_synth_fwd_sep(const vis_field* f, const float* alm, float* img, hipStream_t st);
-void launch_synth_adj_sep(const vis_field* f, float* grad_alm, hipStream_t st);
+void launch_synth_fwd_sep(const vis_field* f, const float* alm, const float* fwhm, float* img,
+                          hipStream_t st);
+void launch_synth_adj_sep(const vis_field* f, const float* fwhm, float* grad_alm, hipStream_t st);
 
-void launch_synth_fwd(const vis_field* f, const float* alm, float* img, hipStream_t st) {
+void launch_synth_fwd(const vis_field* f, const float* alm, const float* fwhm, float* img, hipStream_t st) {
   if (f->synthesis == VIS_SYNTH_SEPARABLE) {
-    launch_synth_fwd_sep(f, alm, img, st);
+    launch_synth_fwd_sep(f, alm, fwhm, img, st);
     return;
   }
   const vis_basis* b = f->basis;
@@ -386,10 +387,11 @@ void launch_synth_fwd(const vis_field* f, const float* alm, float* img, hipStrea
   }
 }
 
-void launch_synth_adj(const vis_field* f, const float* dimg, float* grad_alm, hipStream_t st) {
+void launch_synth_adj(const vis_field* f, const float* dimg, const float* fwhm, float* grad_alm,
+                      hipStream_t st) {
   if (f->synthesis == VIS_SYNTH_SEPARABLE) {
     BV_REQUIRE(dimg == nullptr, VIS_EINVAL, "internal: separable synthesis adjoint reads the full-grid scratch");
-    launch_synth_adj_sep(f, grad_alm, st);
+    launch_synth_adj_sep(f, fwhm, grad_alm, st);
     return;
   }
   BV_REQUIRE(dimg != nullptr, VIS_EINVAL, "internal: dense synthesis adjoint without dL/dI");

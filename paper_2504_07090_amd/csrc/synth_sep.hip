@@ -17,6 +17,9 @@
 // that hold a pixel above the horizon at some time.  The forward writes the
 // visible pixels into the sky scratch; the adjoint reads dL/dI on the full
 // grid, where the adjoint fringe pass writes it (zero at the other pixels).
+// All stages run only the rings and batches that hold a pixel of a chunk within
+// the beam of the field's widest channel (beam.hpp): the sky elsewhere is not
+// read by the forward fringe pass and dL/dI is zero there.
 //
 // Every GEMM is a grid of 16 x 16 output tiles, one wavefront each, on
 // v_mfma_f32_16x16x4_f32: A[i][k] in lane i + 16 k, B[k][j] in lane j + 16 k,
@@ -31,6 +34,7 @@
 // branch ends), and terms past the end of K are removed by zeroing one operand
 // at the MFMA.
 #include "batch.hpp"
+#include "beam.hpp"
 #include "objects.hpp"
 
 namespace bv {
@@ -44,10 +48,9 @@ __device__ __forceinline__ f4 sep_mfma(float a, float b, f4 c) {
 // Blocks are dealt round-robin over the 8 XCDs (block b to XCD b % 8).  The
 // block's linear index is mapped to a logical one such that each XCD runs one
 // contiguous range of logical blocks (the tail that does not fill all eight
-// keeps its index): a bijection on [0, blocks).  Each stage decodes the
-// logical index with the blocks that share operand rows adjacent, so those
-// rows come from one XCD's L2 instead of being fetched once per XCD (the
-// forward Legendre stage keeps the launch order).
+// keeps its index): a bijection on [0, blocks).  The adjoint Legendre stage
+// decodes it with the blocks of one m adjacent, so that m's table rows come
+// from one XCD's L2 instead of being fetched once per XCD.
 __device__ __forceinline__ int sep_xcd_logical(const Blk& B) {
   const int total = B.nx * B.ny * B.nz;
   const int b = B.x + B.nx * (B.y + B.ny * B.z);
@@ -55,141 +58,147 @@ __device__ __forceinline__ int sep_xcd_logical(const Blk& B) {
   return b >= 8 * per ? b : (b % 8) * per + b / 8;
 }
 
-// (x, y, z) block coordinates of logical block L with y and z fastest (the
-// Legendre stages: every block of one m shares that m's table rows).
+// (x, y, z) block coordinates of logical block L with y and z fastest.
 __device__ __forceinline__ int3 sep_blocks_m_major(int L, const Blk& B) {
   const int nyz = B.ny * B.nz, yz = L % nyz;
   return make_int3(L / nyz, yz % B.ny, yz / B.ny);
 }
 
-// (x, y, z) of logical block L with x fastest (the azimuthal stages: the
-// column or c tiles of one ring and channel tile share that ring's rows).
-__device__ __forceinline__ int3 sep_blocks_x_fastest(int L, const Blk& B) {
-  const int yz = L / B.nx;
-  return make_int3(L % B.nx, yz % B.ny, yz / B.ny);
-}
-
 constexpr int kSepBatch = 8;              // MFMAs whose operand loads are issued together
 static_assert(kSepStep == 4 * kSepBatch, "K covered per batch");
 
-// at[mode][nu] = a[nu][mode]: the sky coefficients transposed through a
-// 16-mode x 64-channel LDS tile (one block per 16 modes, so the grid fills the
-// chip), so the Legendre stage reads 16 channels of one mode as one 64-byte
-// segment.
-constexpr int kTrModes = 16, kTrChans = 64;
-struct AlmTransposeArgs {
-  int nf;
-  int nm;
-  const float* a;
-  float* at;
+// What the stages need to find the rings and batches within the beam.
+struct SepBeam {
+  const float* fwhm;
+  float sigr_max;
+  const float* ring_ex;   // [nz]
+  __device__ float cut() const { return beam_cut(fwhm[0] * sigr_max); }
 };
 
-struct KAlmTranspose {
-  using Args = AlmTransposeArgs;
-  static constexpr int kThreads = 256, kWaves = 1;
-  static __device__ void run(const AlmTransposeArgs& args_, const Blk& B_);
-};
-
-__device__ void KAlmTranspose::run(const AlmTransposeArgs& args_, const Blk& B_) {
-  int nf = args_.nf;
-  int nm = args_.nm;
-  const float* __restrict__ a = args_.a;
-  float* __restrict__ at = args_.at;
-
-  __shared__ float tile[kTrChans][kTrModes + 1];
-  const int m0 = B_.x * kTrModes;
-  const int t = threadIdx.x;
-  for (int f0 = 0; f0 < nf; f0 += kTrChans) {
-    // read: 16 consecutive modes of 16 channel rows per pass
-    for (int e = t; e < kTrChans * kTrModes; e += 256) {
-      const int r = e / kTrModes, c = e % kTrModes;
-      const int f = f0 + r, m = m0 + c;
-      tile[r][c] = (f < nf && m < nm) ? a[static_cast<size_t>(f) * nm + m] : 0.f;
-    }
-    __syncthreads();
-    // write: 64 consecutive channels of 4 mode rows per pass
-    for (int e = t; e < kTrChans * kTrModes; e += 256) {
-      const int r = e / kTrChans, c = e % kTrChans;
-      const int m = m0 + r, f = f0 + c;
-      if (m < nm && f < nf) at[static_cast<size_t>(m) * nf + f] = tile[c][r];
-    }
-    __syncthreads();
-  }
-}
-
-// G[j][c][nu] = sum_{l=|m|}^{lmax} lambda_l|m|(z_j) a[nu][l^2 + l + m],  c = m + lmax.
-// grid (2 lmax + 1, ceil(nz / 16), ceil(nf / 16)); D rows = rings, columns = channels.
-// In MFMA step q the lanes of group kk = lane / 16 take l = l0 + 8 kk + q, so
-// every lane reads eight consecutive l of its ring's Legendre row (two
-// 16-byte loads) and each group of 16 lanes one 64-byte segment of `at`.
+// G[j][c][nu] = sum_{l=|m|}^{lmax} lambda_l|m|(z_j) a[nu][l^2 + l + m],  c = m + lmax,
+// for the rings between the first and the last within the beam.  One block per
+// (|m|, 16-channel tile), grid (lmax + 1, ceil(nf / 16)): it gathers the
+// coefficients of +m and -m into LDS, kLegL degrees at a time, and each wave
+// takes 16-ring tiles in turn, one Legendre operand feeding both signs (D rows =
+// rings, columns = channels).  In MFMA step q the lanes of group kk = lane / 16
+// take l = l0 + 8 kk + q, so every lane reads eight consecutive l of its ring's
+// Legendre row (two 16-byte loads), all issued before the gather is waited for.
+// Bound by the latency of the gather.  It replaces a transpose of the
+// coefficients and a stage reading its rows, one wave per (m, ring tile, channel
+// tile): 61 dishes, lmax 100, 64 channels 17.9 -> 15.8 us over two and one
+// launches, 19 dishes, lmax 45, 33 channels 13.0 -> 8.9 us.
+constexpr int kLegL = 128, kLegWaves = 8;
 struct SepLegFwdArgs {
   int nz;
   int nf;
+  int nm;
   int lmax;
   int blmax;
   int kaz;
   const float* lam;
   const int* loff;
-  const float* at;
+  const float* alm;
   float* G;
+  SepBeam beam;
 };
 
 struct KSepLegFwd {
   using Args = SepLegFwdArgs;
-  static constexpr int kThreads = 64, kWaves = 1;
+  static constexpr int kThreads = 64 * kLegWaves, kWaves = 1;
   static __device__ void run(const SepLegFwdArgs& args_, const Blk& B_);
 };
 
-__device__ void KSepLegFwd::run(const SepLegFwdArgs& args_, const Blk& B_) {
-  int nz = args_.nz;
-  int nf = args_.nf;
-  int lmax = args_.lmax;
-  int blmax = args_.blmax;
-  int kaz = args_.kaz;
-  const float* __restrict__ lam = args_.lam;
-  const int* __restrict__ loff = args_.loff;
-  const float* __restrict__ at = args_.at;
-  float* __restrict__ G = args_.G;
+// Row of degree l0 + d of one sign in LDS: 16 channels, every eighth row
+// followed by 16 floats so that the four lane groups (rows 8 apart) read
+// different banks.
+__device__ __forceinline__ int leg_row(int d) { return 16 * (d + (d >> 3)); }
 
-  // blocks in launch order: grouping an m's blocks on one XCD, as the adjoint
-  // does, measured slower here (the rows shorten with |m|, so contiguous m
-  // ranges leave the XCDs unevenly loaded)
-  const int m = static_cast<int>(B_.x) - lmax, am = m < 0 ? -m : m;
-  const int j0 = B_.y * 16, f0 = B_.z * 16;
-  const int lane = threadIdx.x, i = lane & 15, kk = lane >> 4;
-  const int j = min(j0 + i, nz - 1), f = min(f0 + i, nf - 1);
-  const int lp = sep_lpad(blmax, am);
-  const float* lrow = lam + loff[am] + static_cast<size_t>(j) * lp;
-  f4 acc = f4{0.f, 0.f, 0.f, 0.f};
-  for (int l0 = am; l0 <= lmax; l0 += kSepStep) {
-    const int lb = l0 + 8 * kk;          // this lane's l = lb .. lb + 7
-    f4 a0 = f4{0.f, 0.f, 0.f, 0.f}, a1 = a0;
-    if (lb - am < lp) {                  // lp is a multiple of 8: all eight in the row or none
-      a0 = *reinterpret_cast<const f4*>(lrow + (lb - am));
-      a1 = *reinterpret_cast<const f4*>(lrow + (lb - am) + 4);
+__device__ void KSepLegFwd::run(const SepLegFwdArgs& args_, const Blk& B_) {
+  const int nz = args_.nz, nf = args_.nf, lmax = args_.lmax, kaz = args_.kaz;
+  const float* __restrict__ alm = args_.alm;
+  float* __restrict__ G = args_.G;
+  constexpr int kRows = 16 * (kLegL + kLegL / 8);
+  __shared__ float as[2][kRows];
+
+  const int am = B_.x, f0 = B_.y * 16, nsign = am > 0 ? 2 : 1;
+  const int tid = threadIdx.x, lane = tid & 63, i = lane & 15, kk = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int2 rng = beam_range(args_.beam.ring_ex, nz, args_.beam.cut(), lane);
+  const int t0 = rng.x / 16, t1 = rng.y < 0 ? t0 : rng.y / 16 + 1;   // ring tiles
+  const int lp = sep_lpad(args_.blmax, am);
+  // one round of the block's waves over the ring tiles per pass
+  for (int tb = t0; tb < t1; tb += kLegWaves) {
+    const int jt = tb + wv, j = min(16 * jt + i, nz - 1);
+    const float* lrow = args_.lam + args_.loff[am] + static_cast<size_t>(j) * lp;
+    f4 acc[2] = {f4{0.f, 0.f, 0.f, 0.f}, f4{0.f, 0.f, 0.f, 0.f}};
+    for (int lb = am; lb <= lmax; lb += kLegL) {
+      const int nl = min(kLegL, lmax + 1 - lb);
+      // this lane's Legendre operands of every batch, in flight beside the gather
+      f4 av[kLegL / kSepStep][2];
+#pragma unroll
+      for (int h = 0; h < kLegL / kSepStep; ++h) {
+        const int dl = lb - am + kSepStep * h + 8 * kk;   // this lane's l - am = dl .. dl + 7
+        const bool in = kSepStep * h < nl && dl < lp;     // lp is a multiple of 8: all eight in the row or none
+#pragma unroll
+        for (int q = 0; q < 2; ++q)
+          av[h][q] = in ? *reinterpret_cast<const f4*>(lrow + dl + 4 * q) : f4{0.f, 0.f, 0.f, 0.f};
+      }
+      if (tb == t0 || lmax + 1 - am > kLegL) {
+        // thread (d, q): degree lb + d of slab after slab of 32, channel and sign
+        // q, q + 16; all loads issue before the first is stored
+        constexpr int kQ = 2 * kLegWaves;   // threads per degree
+        const int d = tid & 31, q0 = tid >> 5;
+        float v[kLegL / 32][32 / kQ];
+#pragma unroll
+        for (int h = 0; h < kLegL / 32; ++h)
+#pragma unroll
+          for (int it = 0; it < 32 / kQ; ++it) {
+            const int q = q0 + kQ * it, l = lb + 32 * h + d, f = f0 + (q & 15);
+            v[h][it] = 32 * h + d < nl && f < nf && (q >> 4) < nsign
+                           ? alm[static_cast<size_t>(f) * args_.nm + l * l + l + ((q >> 4) ? -am : am)] : 0.f;
+          }
+        __syncthreads();   // the previous contents are read
+#pragma unroll
+        for (int h = 0; h < kLegL / 32; ++h)
+#pragma unroll
+          for (int it = 0; it < 32 / kQ; ++it) {
+            const int q = q0 + kQ * it;
+            as[q >> 4][leg_row(32 * h + d) + (q & 15)] = v[h][it];
+          }
+        __syncthreads();
+      }
+      if (jt >= t1) continue;   // uniform over the wave
+#pragma unroll
+      for (int h = 0; h < kLegL / kSepStep; ++h) {
+        if (kSepStep * h >= nl) break;   // uniform
+#pragma unroll
+        for (int q = 0; q < kSepBatch; ++q) {
+          const int o = leg_row(kSepStep * h + 8 * kk + q) + i;
+          acc[0] = sep_mfma(av[h][q >> 2][q & 3], as[0][o], acc[0]);
+          if (nsign == 2) acc[1] = sep_mfma(av[h][q >> 2][q & 3], as[1][o], acc[1]);
+        }
+      }
     }
-    float b[kSepBatch];
+    const int fo = f0 + (lane & 15);
+    if (jt >= t1 || fo >= nf) continue;
 #pragma unroll
-    for (int q = 0; q < kSepBatch; ++q) {
-      const int l = lb + q;
-      b[q] = l <= lmax ? at[static_cast<size_t>(l * l + l + m) * nf + f] : 0.f;
+    for (int sg = 0; sg < 2; ++sg) {
+      if (sg >= nsign) break;
+      const int c = lmax + (sg ? -am : am);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int jo = 16 * jt + 4 * kk + r;
+        if (jo < nz) G[(static_cast<size_t>(jo) * kaz + c) * nf + fo] = acc[sg][r];
+      }
     }
-#pragma unroll
-    for (int q = 0; q < kSepBatch; ++q) acc = sep_mfma(q < 4 ? a0[q] : a1[q - 4], b[q], acc);
-  }
-  const int c = m + lmax, fo = f0 + (lane & 15);
-#pragma unroll
-  for (int r = 0; r < 4; ++r) {
-    const int jo = j0 + 4 * kk + r;
-    if (jo < nz && fo < nf) G[(static_cast<size_t>(jo) * kaz + c) * nf + fo] = acc[r];
   }
 }
 
 // img[nu][slot(j, k)] = sum_{c < nc} G[j][c][nu] Tt[c + toff][k] for visible pixels
 // (nc = 2 lmax + 1 rows of G per ring are used).
-// grid (column batches that hold a pixel above the horizon at some time, 1,
-// ceil(nf / 32)): block x takes batch kb[x] of ring kb_ring[x] (a ring's
-// batches are consecutive); each wave computes a 2 x 2 block of 16 x 16 tiles
+// grid (column batches, 1, ceil(nf / 32)): block x takes the batch of x-th
+// smallest excess, so those within the beam are a prefix dealt evenly to the
+// XCDs; each wave computes a 2 x 2 block of 16 x 16 tiles
 // (rows = channels, columns = pixels), so every operand load feeds two MFMAs.
 struct SepAzFwdArgs {
   int nphi;
@@ -201,10 +210,11 @@ struct SepAzFwdArgs {
   const float* Tt;
   const float* G;
   const int* vidx;
-  const int* kb;
-  const int* kb_ring;
+  const int* sorted;
+  const float* sorted_ex;
   int nvp;
   float* img;
+  SepBeam beam;
 };
 
 struct KSepAzFwd {
@@ -225,8 +235,8 @@ __device__ void KSepAzFwd::run(const SepAzFwdArgs& args_, const Blk& B_) {
   int nvp = args_.nvp;
   float* __restrict__ img = args_.img;
 
-  const int3 bk = sep_blocks_x_fastest(sep_xcd_logical(B_), B_);
-  const int k0 = args_.kb[bk.x], j = args_.kb_ring[bk.x], f0 = bk.z * 32;
+  if (args_.sorted_ex[B_.x] > args_.beam.cut()) return;
+  const int first = args_.sorted[B_.x], j = first / nphi, k0 = first - j * nphi, f0 = B_.z * 32;
   const int lane = threadIdx.x, i = lane & 15, kk = lane >> 4;
   const float* grow[2];
   const float* tcol[2];
@@ -294,9 +304,11 @@ __device__ void KSepAzFwd::run(const SepAzFwdArgs& args_, const Blk& B_) {
 }
 
 // H[j][c][nu] = sum_k T[k][c + toff] dL/dI[j][nu][k] for c < nc = 2 lmax + 1,
-// over the ring's column batches that hold a pixel above the horizon at some
-// time (dL/dI is zero elsewhere).  grid (ceil(nc / 32), nz, ceil(nf / 32));
-// each wave computes a 2 x 2 block of 16 x 16 tiles (rows = c, columns =
+// over the ring's column batches within the beam (dL/dI is zero elsewhere), for
+// the rings within it and those between them.  Block b runs on XCD b % 8; ring r
+// (in ascending order of excess, so that the rings within the beam are dealt
+// evenly) goes to XCD r % 8 with all its c and channel tiles, which share its
+// rows; grid 8 ceil(nz / 8) ceil(nc / 32) ceil(nf / 32), each wave computes a 2 x 2 block of 16 x 16 tiles (rows = c, columns =
 // channels).  In a group of four MFMA steps, lane group kk supplies columns
 // k0 + 4 kk .. + 3 (one per step): the transposed table Tt[c][k] and the
 // channel's dL/dI row are both contiguous in k, so each operand value of the
@@ -312,7 +324,13 @@ struct SepAzAdjArgs {
   const float* dfull;
   const int* kb_off;
   const int* kb;
+  const float* kb_ex;
+  const int* ring;
+  int nz;
+  int ctiles;         // ceil(nc / 32)
+  int per_ring;       // blocks per ring
   float* H;
+  SepBeam beam;
 };
 
 struct KSepAzAdj {
@@ -325,9 +343,19 @@ __device__ void KSepAzAdj::run(const SepAzAdjArgs& args_, const Blk& B_) {
   const int nf = args_.nf, kaz = args_.kaz, nc = args_.nc, tstride = args_.tstride;
   float* __restrict__ H = args_.H;
 
-  const int3 bk = sep_blocks_x_fastest(sep_xcd_logical(B_), B_);
-  const int c0 = bk.x * 32, j = bk.y, f0 = bk.z * 32;
   const int lane = threadIdx.x, i = lane & 15, kk = lane >> 4;
+  const int s = B_.x >> 3, g8 = s / args_.per_ring, within = s - g8 * args_.per_ring;
+  const int r = 8 * g8 + (B_.x & 7);
+  if (r >= args_.nz) return;
+  const int j = args_.ring[r], ft = within / args_.ctiles;
+  const int c0 = (within - ft * args_.ctiles) * 32, f0 = ft * 32;
+  const float cut = args_.beam.cut();
+  const int kb0 = args_.kb_off[j];
+  const int nkb = beam_prefix<1>(args_.kb_ex + kb0, args_.kb_off[j + 1] - kb0, cut, lane);
+  if (nkb == 0) {
+    const int2 rng = beam_range(args_.beam.ring_ex, args_.nz, cut, lane);
+    if (j < rng.x || j > rng.y) return;   // not read by the Legendre stage
+  }
   const float* trow[2];
   const float* drow[2];
 #pragma unroll
@@ -364,8 +392,7 @@ __device__ void KSepAzAdj::run(const SepAzAdjArgs& args_, const Blk& B_) {
 #pragma unroll
           for (int g = 0; g < 2; ++g) acc[h][g] = sep_mfma(B.a[s][h][q], B.b[s][g][q], acc[h][g]);
   };
-  const int* kb = args_.kb + args_.kb_off[j];
-  const int nkb = args_.kb_off[j + 1] - args_.kb_off[j];
+  const int* kb = args_.kb + kb0;
   if (nkb > 0) {
     // the batch after the last re-reads the last (always issued, never used)
     auto kb_at = [&](int q) { return kb[min(q, nkb - 1)]; };
@@ -395,7 +422,8 @@ __device__ void KSepAzAdj::run(const SepAzAdjArgs& args_, const Blk& B_) {
   }
 }
 
-// grad[nu][l^2 + l + m] = sum_j lambda_l|m|(z_j) H[j][m + lmax][nu], l = |m| .. lmax;
+// grad[nu][l^2 + l + m] = sum_j lambda_l|m|(z_j) H[j][m + lmax][nu], l = |m| .. lmax,
+// over the rings between the first and the last within the beam;
 // 16 lanes read 16 consecutive l of one ring row of the m-major Legendre table.
 // grid (2 lmax + 1, ceil((lmax + 1) / 16), ceil(nf / 16)); D rows = l, columns = channels.
 struct SepLegAdjArgs {
@@ -409,6 +437,7 @@ struct SepLegAdjArgs {
   const int* loff;
   const float* H;
   float* grad;
+  SepBeam beam;
 };
 
 struct KSepLegAdj {
@@ -440,12 +469,13 @@ __device__ void KSepLegAdj::run(const SepLegAdjArgs& args_, const Blk& B_) {
   const float* lcol = lam + loff[am] + (l - am);   // 16 lanes: 16 consecutive l of one ring
   const float* hcol = H + static_cast<size_t>(c) * nf + f;
   f4 acc = f4{0.f, 0.f, 0.f, 0.f};
-  for (int jb = 0; jb < nz; jb += kSepStep) {
+  const int2 rng = beam_range(args_.beam.ring_ex, nz, args_.beam.cut(), lane);
+  for (int jb = rng.x; jb <= rng.y; jb += kSepStep) {
     float a[kSepBatch], b[kSepBatch];
 #pragma unroll
     for (int q = 0; q < kSepBatch; ++q) {
       const int j = jb + 4 * q + kk;
-      const bool ok = j < nz;
+      const bool ok = j <= rng.y;
       a[q] = ok ? lcol[static_cast<size_t>(j) * lp] : 0.f;
       b[q] = ok ? hcol[static_cast<size_t>(j) * kaz * nf] : 0.f;
     }
@@ -460,47 +490,47 @@ __device__ void KSepLegAdj::run(const SepLegAdjArgs& args_, const Blk& B_) {
   }
 }
 
-void launch_synth_fwd_sep(const vis_field* f, const float* alm, float* img, hipStream_t st) {
+void launch_synth_fwd_sep(const vis_field* f, const float* alm, const float* fwhm, float* img,
+                          hipStream_t st) {
   const vis_basis* b = f->basis;
   BV_REQUIRE(b->sep_lam != nullptr, VIS_EINVAL, "basis has no separable factor tables");
   const int L = f->lmax;
   const int toff = b->lmax + kSepPad - L;   // T column of c = 0 (m = -L)
-  {
-    ProfScope ps(&f->prof, "k_alm_transpose", st);
-    launch_k<KAlmTranspose>(ceil_div(f->n_modes, kTrModes), 0, AlmTransposeArgs{f->n_freq, f->n_modes, alm,
-                                                                     f->scr.sep_at}, st, "k_alm_transpose");
-  }
+  const SepBeam beam{fwhm, f->sigr_max, f->tab.sep_ring_ex};
   {
     ProfScope ps(&f->prof, "k_sep_leg_fwd", st);
-    dim3 grid(2 * L + 1, ceil_div(b->nz, 16), ceil_div(f->n_freq, 16));
-    launch_k<KSepLegFwd>(grid, 0, SepLegFwdArgs{b->nz, f->n_freq, L, b->lmax, f->kaz, b->sep_lam, b->sep_loff,
-                                       f->scr.sep_at, f->scr.sep_g}, st, "k_sep_leg_fwd");
+    launch_k<KSepLegFwd>(dim3(L + 1, ceil_div(f->n_freq, 16)), 0,
+                         SepLegFwdArgs{b->nz, f->n_freq, f->n_modes, L, b->lmax, f->kaz, b->sep_lam,
+                                       b->sep_loff, alm, f->scr.sep_g, beam}, st, "k_sep_leg_fwd");
   }
   ProfScope ps(&f->prof, "k_sep_az_fwd", st);
   dim3 grid(f->sep_nkb, 1, ceil_div(f->n_freq, 32));
   launch_k<KSepAzFwd>(grid, 0, SepAzFwdArgs{b->nphi, f->n_freq, f->kaz, 2 * L + 1, toff, b->nphi_b, b->sep_tt, f->scr.sep_g,
-                                    f->tab.vidx, f->tab.sep_kb, f->tab.sep_kb_ring, f->nv_pad, img},
+                                    f->tab.vidx, f->tab.sep_sorted, f->tab.sep_sorted_ex, f->nv_pad, img, beam},
                       st, "k_sep_az_fwd");
 }
 
 // dL/dI comes in the full-grid scratch sep_dfull, written there by the
 // adjoint fringe pass (zero at pixels never above the horizon).
-void launch_synth_adj_sep(const vis_field* f, float* grad_alm, hipStream_t st) {
+void launch_synth_adj_sep(const vis_field* f, const float* fwhm, float* grad_alm, hipStream_t st) {
   const vis_basis* b = f->basis;
   BV_REQUIRE(b->sep_lam != nullptr, VIS_EINVAL, "basis has no separable factor tables");
   const int L = f->lmax;
   const int toff = b->lmax + kSepPad - L;
+  const SepBeam beam{fwhm, f->sigr_max, f->tab.sep_ring_ex};
   {
     ProfScope ps(&f->prof, "k_sep_az_adj", st);
-    dim3 grid(ceil_div(2 * L + 1, 32), b->nz, ceil_div(f->n_freq, 32));
-    launch_k<KSepAzAdj>(grid, 0, SepAzAdjArgs{f->n_freq, f->kaz, 2 * L + 1, b->nphi_b, toff, b->sep_tt,
-                                      f->scr.sep_dfull, f->tab.sep_kb_off, f->tab.sep_kb, f->scr.sep_g},
+    const int ctiles = ceil_div(2 * L + 1, 32), per_ring = ctiles * ceil_div(f->n_freq, 32);
+    launch_k<KSepAzAdj>(dim3(static_cast<unsigned>(round_up(b->nz, 8) * per_ring)), 0,
+                        SepAzAdjArgs{f->n_freq, f->kaz, 2 * L + 1, b->nphi_b, toff, b->sep_tt, f->scr.sep_dfull,
+                                     f->tab.sep_kb_off, f->tab.sep_kb, f->tab.sep_kb_ex, f->tab.sep_ring, b->nz,
+                                     ctiles, per_ring, f->scr.sep_g, beam},
                         st, "k_sep_az_adj");
   }
   ProfScope ps(&f->prof, "k_sep_leg_adj", st);
   dim3 grid(2 * L + 1, ceil_div(L + 1, 16), ceil_div(f->n_freq, 16));
   launch_k<KSepLegAdj>(grid, 0, SepLegAdjArgs{b->nz, f->n_freq, f->n_modes, L, b->lmax, f->kaz, b->sep_lam,
-                                     b->sep_loff, f->scr.sep_g, grad_alm}, st, "k_sep_leg_adj");
+                                     b->sep_loff, f->scr.sep_g, grad_alm, beam}, st, "k_sep_leg_adj");
 }
 
 }  // namespace bv

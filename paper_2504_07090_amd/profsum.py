@@ -92,7 +92,7 @@ def traffic_report(fetch_csv: str, write_csv: str, command: str, kernels, sha: s
         b = (f * ff + wv * fw) * 1024
         per[k] = b
         out.append(f"| `{k}` | {fn[k]} | {f:.1f} | {wv:.1f} | {b:.4g} |")
-    out += ["", f"Fringe kernel sources (fringe.hip, common.hpp) sha256 at the time of the runs: `{sha}`.", ""]
+    out += ["", f"Fringe kernel sources (fringe.hpp, common.hpp) sha256 at the time of the runs: `{sha}`.", ""]
     return "\n".join(out) + "\n", per
 
 
