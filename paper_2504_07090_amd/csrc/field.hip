@@ -481,6 +481,8 @@ static void carve_field(vis_field* f, Carver& cv, int n_tchunk) {
   T.bl_ant = cv.take<int2>(f->n_bl);
   T.bl_u = cv.take<int>(f->n_bl);
   T.bl_pos = cv.take<int4>(f->n_bl);
+  T.bl_pack = cv.take<int2>(f->n_bl);
+  T.u_order = cv.take<int2>(f->n_ubl);
   T.u_off = cv.take<int>(f->n_ubl + 1);
   T.u_list = cv.take<int>(f->n_bl);
   T.a_off = cv.take<int>(f->n_ant + 1);
@@ -789,6 +791,11 @@ vis_status vis_field_create(const vis_basis* basis, const vis_field_desc* desc, 
     up(T.bl_ant, bl_ant, s);
     up(T.bl_u, bl_u, s);
     up(T.bl_pos, bl_pos, s);
+    std::vector<int2> bl_pack;
+    std::vector<int2> u_order;
+    staged_tables(f->n_ant, f->n_bl, f->n_ubl, bl_ant, bl_u, bl_pos, u_off, bl_pack, u_order);
+    up(T.bl_pack, bl_pack, s);
+    up(T.u_order, u_order, s);
     up(T.u_off, u_off, s);
     up(T.u_list, u_list, s);
     up(T.a_off, a_off, s);

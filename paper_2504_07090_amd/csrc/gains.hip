@@ -13,6 +13,8 @@
 //   dL/dg_a = sum_{(a, j)} c_aj g_j conj(V_aj) + sum_{(i, a)} conj(c_ia) g_i V_ia.
 // One 256-thread block per (t, nu) keeps the gains and unique visibilities of
 // that slice in LDS; every reduction runs in a fixed order.
+#include <algorithm>
+
 #include "batch.hpp"
 #include "objects.hpp"
 
@@ -48,6 +50,8 @@ struct GainArgs {
   int gstride;
   int split;   // the adjoint multiplies the coefficients as FP16 hi + lo pairs
   int tslab;   // consecutive times per block
+  const int2* bl_pack;   // see KGainsStaged
+  const int2* u_order;
 };
 
 // Sum of v over groups of `width` consecutive lanes (width a power of two
@@ -237,23 +241,26 @@ __device__ __forceinline__ float coef_term(const float2* om, int src, int comp, 
   return neg ? -v : v;
 }
 
-// Plan entries a thread of a 256-thread block holds in registers for a whole
-// slab (entries tid and tid + 256); the rest are read per slice.
+// Plan entries a thread of an NT-thread block holds in registers for a whole
+// slab (entries tid and tid + NT); the rest are read per slice.
 constexpr int kPlanRegs = 2;
 
+template <int NT>
 __device__ __forceinline__ void write_coefficients(const GainArgs& a, const float2* om, size_t slice,
                                                    int tid, const int4* plan_r) {
   // split layout: power-of-two scale from the largest |omega| component
   // (|G| <= 2 max |omega|), found by the whole block
   float scale = 1.0f;
   if (a.split) {
-    __shared__ float red_max[4];
+    __shared__ float red_max[NT / 64];
     float mx = 0.f;
-    for (int u = tid; u < a.nubl; u += blockDim.x) mx = fmaxf(mx, fmaxf(fabsf(om[u].x), fabsf(om[u].y)));
+    for (int u = tid; u < a.nubl; u += NT) mx = fmaxf(mx, fmaxf(fabsf(om[u].x), fabsf(om[u].y)));
     for (int o = 32; o >= 1; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
     if ((tid & 63) == 0) red_max[tid >> 6] = mx;
     __syncthreads();
-    mx = fmaxf(fmaxf(red_max[0], red_max[1]), fmaxf(red_max[2], red_max[3]));
+    mx = red_max[0];
+#pragma unroll
+    for (int w = 1; w < NT / 64; ++w) mx = fmaxf(mx, red_max[w]);
     __syncthreads();   // red_max is reused by the next slice of this block
     if (mx > 0.f && isfinite(mx)) {
       int ex;
@@ -285,10 +292,10 @@ __device__ __forceinline__ void write_coefficients(const GainArgs& a, const floa
   };
 #pragma unroll
   for (int q = 0; q < kPlanRegs; ++q) {
-    const int e = tid + 256 * q;
+    const int e = tid + NT * q;
     if (e < a.gstride) entry(e, plan_r[q]);
   }
-  for (int e = tid + 256 * kPlanRegs; e < a.gstride; e += 256) entry(e, a.cplan[e]);
+  for (int e = tid + NT * kPlanRegs; e < a.gstride; e += NT) entry(e, a.cplan[e]);
 }
 
 // Gains pass over (t, nu) slices.  Pass 1 walks the physical baselines in
@@ -301,8 +308,8 @@ __device__ __forceinline__ void write_coefficients(const GainArgs& a, const floa
 // forms each baseline's contribution to its unique baseline's omega and to its
 // two antennas' gradients and stores them in LDS at the baseline's positions
 // in the per-unique and per-antenna lists, so the sums that follow run over
-// contiguous LDS ranges.  Otherwise (one slice per block) the sums walk the
-// lists and recompute the terms.  Each list gets `w` lanes that combine their
+// contiguous LDS ranges.  Fields beyond KGainsStaged's limits run one slice per
+// block, and their sums walk the lists and recompute the terms.  Each list gets `w` lanes that combine their
 // partial sums with a fixed butterfly, so every result has a fixed order.
 constexpr int kGainsMaxPerThread = 8;
 
@@ -545,8 +552,219 @@ __device__ void KGains<SORTED, MODE>::run(const GainArgs& a, const Blk& B) {
       }
     }
     __syncthreads();
-    write_coefficients(a, om, slice, tid, plan_r);
+    write_coefficients<256>(a, om, slice, tid, plan_r);
   }
+}
+
+// Staged gains pass: one block per channel and slab of times, each thread with
+// the packed table entries of its baselines (tid + NT q) in registers for the
+// slab (512 threads of up to 9 baselines, or 1024 of up to 8).  Per slice the threads form every baseline's cotangent once, from
+// coalesced loads issued in the slice before, and its terms: first the omega
+// term goes to LDS in u_list order and 16 lanes per unique baseline add its
+// range (lists in descending length, so that the four groups of a wave are
+// equally long); then h = c conj(V) takes its place in the lexicographic order
+// of the baselines, and 16 lanes per antenna a add sum_b H_ab g_b, H_ab = h_ab
+// for b > a and conj(h_ba) for b < a, at indices advanced from a and b.  Sums over
+// 16 lanes run on the row-rotating vector operations.  Taken where SORTED's three
+// staged terms per baseline do not fit (62 to 128 dishes); the list walks in
+// memory that such fields ran before gathered each baseline's data three times
+// with one or two lanes per list: 127 dishes, 96 channels, 97 times 1484 -> 367
+// us (600 MB of data: 128 us at a copy's rate), 91 dishes, 48 channels, 45 times
+// (cotangent given) 128 -> 41 us.  Bound by vector issue (58% of the time at 127
+// dishes) and the barriers between its phases.  Tried at 127 dishes: 512
+// threads of 16 baselines with the table read from L2 (552 us), and 64
+// registers for two 1024-thread blocks per CU (686 us, spills).  At 61 dishes
+// SORTED is the faster one, 34 against 38 us.
+__host__ __device__ constexpr int staged_threads(int cap) { return cap <= 2048 ? 256 : cap <= 4608 ? 512 : 1024; }
+
+// Packed table entry of one baseline (i, j): LDS byte offsets of g_i and g_j in x,
+// of V_u and of the omega term's place in y, and the sign bit for b = -b_u.
+static int2 pack_entry(int i, int j, int u, int pos, bool neg) {
+  return make_int2(static_cast<int>(8u * i | (8u * j) << 13),
+                   static_cast<int>(8u * u | (8u * pos) << 13 << 2 | (neg ? 1u << 31 : 0u)));
+}
+static_assert(8 * (kStagedMaxUnique - 1) < (1 << 15) && 8 * (kStagedMaxBaselines - 1) < (1 << 16),
+              "packed fields: 13 + 13 and 15 + 16 + 1 bits");
+
+template <class T>
+__device__ __forceinline__ T& lds_byte(T* base, unsigned off) {
+  return *reinterpret_cast<T*>(reinterpret_cast<char*>(base) + off);
+}
+__device__ __forceinline__ float flip(float x, unsigned sign_bit) {
+  return __uint_as_float(__float_as_uint(x) ^ sign_bit);
+}
+
+// Sum over each row of 16 lanes, in every lane, in a fixed order.
+__device__ __forceinline__ float row_sum(float x) {
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x128, 0xf, 0xf, true));   // rotate by 8
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x124, 0xf, 0xf, true));
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x122, 0xf, 0xf, true));
+  x += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), 0x121, 0xf, 0xf, true));
+  return x;
+}
+
+template <int CAP, int MODE>
+struct KGainsStaged {
+  using Args = GainArgs;
+  static constexpr int kThreads = staged_threads(CAP), kWaves = 4;
+  static __device__ void run(const GainArgs& a, const Blk& B);
+};
+
+template <int CAP, int MODE>
+__device__ void KGainsStaged<CAP, MODE>::run(const GainArgs& a, const Blk& B) {
+  constexpr bool kCot = MODE == kGainAdj || MODE == kGainMap;   // cotangent given
+  constexpr int NT = staged_threads(CAP), NPT = CAP / NT;
+  static_assert(CAP % NT == 0, "whole baselines per thread");
+  __shared__ float2 buf[CAP];                 // omega terms, then h
+  __shared__ float2 g[kStagedMaxAntennas];
+  __shared__ float2 v[kStagedMaxUnique], om[kStagedMaxUnique];
+  __shared__ int2 range[kStagedMaxUnique];    // of the r-th longest list: first | length << 16, unique
+  __shared__ double red[NT / 64];
+  const int f = B.x, tid = threadIdx.x, sub = tid & 15, grp = tid >> 4;
+  const int t0 = B.y * a.tslab, t1 = min(a.nt, t0 + a.tslab);
+  const int n = a.nant;
+  for (int i = tid; i < n; i += NT) g[i] = a.gains[static_cast<size_t>(f) * n + i];
+  for (int r = tid; r < a.nubl; r += NT) range[r] = a.u_order[r];
+  int2 ent[NPT];
+  float2 d_r[NPT], v_r = make_float2(0.f, 0.f);
+#pragma unroll
+  for (int q = 0; q < NPT; ++q) ent[q] = a.bl_pack[min(tid + NT * q, a.nbl - 1)];
+  int4 plan_r[kPlanRegs];
+#pragma unroll
+  for (int q = 0; q < kPlanRegs; ++q) {
+    const int e = tid + NT * q;
+    plan_r[q] = e < a.gstride ? a.cplan[e] : int4{0, 0, 0, 0};
+  }
+  auto fetch = [&](int t) {
+    const size_t sl = static_cast<size_t>(t) * a.nf + f;
+    const float2* din = a.din + sl * a.nbl;
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) d_r[q] = din[min(tid + NT * q, a.nbl - 1)];
+    if (tid < a.nubl) v_r = a.vu[sl * a.nubl + tid];
+  };
+  // body(q) for every baseline of this thread: whole rounds of the block without
+  // a bounds check, then the last, partial one
+  auto baselines = [&](auto body) {
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) {
+      if (NT * (q + 1) <= a.nbl) {   // uniform
+        body(q);
+      } else if (tid + NT * q < a.nbl) {
+        body(q);
+      }
+    }
+  };
+  if (t0 < t1) fetch(t0);
+  for (int t = t0; t < t1; ++t) {
+    const size_t slice = static_cast<size_t>(t) * a.nf + f;
+    // unpack the entries anew in every slice: hoisted, their four LDS offsets
+    // each would not fit in registers
+#pragma unroll
+    for (int q = 0; q < NPT; ++q) asm("" : "+v"(ent[q].x), "+v"(ent[q].y) : "s"(t));
+    if (tid < a.nubl) v[tid] = v_r;
+    for (int u = tid + NT; u < a.nubl; u += NT) v[u] = a.vu[slice * a.nubl + u];
+    __syncthreads();
+    double acc = 0.0;
+    baselines([&](int q) {
+      const unsigned ex = ent[q].x, ey = ent[q].y, neg = ey & 0x80000000u;
+      const float2 G = cmul(lds_byte(g, ex & 0x1fffu), conjf2(lds_byte(g, ex >> 13)));
+      float2 c = d_r[q];
+      if (!kCot) {
+        float2 vk = lds_byte(v, ey & 0x7fffu);
+        vk.y = flip(vk.y, neg);
+        const float2 m = cmul(G, vk);
+        const float rx = c.x - m.x, ry = c.y - m.y;
+        if (MODE == kGainChi2) acc += static_cast<double>(__builtin_fmaf(rx, rx, ry * ry));
+        c = make_float2(-2.f * a.inv_sig2 * rx, -2.f * a.inv_sig2 * ry);
+        d_r[q] = c;   // the cotangent, for h below
+      }
+      float2 w = cmul(conjf2(c), G);
+      w.y = flip(w.y, neg);
+      lds_byte(buf, (ey >> 15) & 0xffffu) = w;
+    });
+    if (MODE == kGainChi2) {
+      for (int o = 32; o >= 1; o >>= 1) acc += __shfl_xor(acc, o);
+      if ((tid & 63) == 0) red[tid >> 6] = acc;
+    }
+    __syncthreads();
+    if (MODE == kGainChi2 && tid == 0) {
+      double tot = 0.0;
+      for (int w = 0; w < NT / 64; ++w) tot += red[w];
+      a.chi_part[slice] = tot * static_cast<double>(a.inv_sig2);
+    }
+    for (int r = grp; r < a.nubl; r += NT / 16) {
+      const int2 o = range[r];
+      const int len = o.x >> 16;
+      const float2* x = buf + (o.x & 0xffff) + sub;
+      float2 p0 = make_float2(0.f, 0.f), p1 = p0;
+      int e = sub;
+      for (; e + 16 < len; e += 32, x += 32) {
+        const float2 x0 = x[0], x1 = x[16];
+        p0.x += x0.x;
+        p0.y += x0.y;
+        p1.x += x1.x;
+        p1.y += x1.y;
+      }
+      if (e < len) {
+        p0.x += x[0].x;
+        p0.y += x[0].y;
+      }
+      const float2 s = make_float2(row_sum(p0.x + p1.x), row_sum(p0.y + p1.y));
+      if (sub == 0) om[o.y] = s;
+    }
+    __syncthreads();
+    if (MODE != kGainMap) {
+      baselines([&](int q) {
+        const unsigned ey = ent[q].y;
+        float2 vk = lds_byte(v, ey & 0x7fffu);
+        vk.y = flip(vk.y, ~ey & 0x80000000u);   // conj(V)
+        buf[tid + NT * q] = cmul(d_r[q], vk);
+      });
+    }
+    if (t + 1 < t1) fetch(t + 1);   // in flight over the rest of this slice
+    write_coefficients<NT>(a, om, slice, tid, plan_r);
+    if (MODE != kGainMap) {
+      __syncthreads();
+      for (int x = grp; x < n; x += NT / 16) {
+        // baseline (x, b), b > x, at row + b; (b, x), b < x, at col, which grows
+        // by `step` from b to b + 16, itself falling by 256
+        const int row = x * (2 * n - x - 1) / 2 - x - 1;
+        int col = sub * (2 * n - sub - 1) / 2 - sub - 1 + x, step = 16 * n - 16 * sub - 152;
+        float2 p[2] = {make_float2(0.f, 0.f), make_float2(0.f, 0.f)};
+        for (int b0 = 0; b0 < n; b0 += 32) {
+#pragma unroll
+          for (int s = 0; s < 2; ++s) {
+            const int b = b0 + 16 * s + sub;
+            if (b < n && b != x) {
+              const float2 hb = buf[b > x ? row + b : col], gb = g[b];
+              const float hy = b > x ? hb.y : -hb.y;
+              p[s].x += hb.x * gb.x - hy * gb.y;
+              p[s].y += hb.x * gb.y + hy * gb.x;
+            }
+            col += step;
+            step -= 256;
+          }
+        }
+        const float2 s = make_float2(row_sum(p[0].x + p[1].x), row_sum(p[0].y + p[1].y));
+        if (sub == 0) a.g_part[slice * n + x] = s;
+      }
+    }
+    __syncthreads();   // buf, v and om are read
+  }
+}
+
+// Tables of KGainsStaged: the packed entry of every baseline, and the u_list
+// ranges of the unique baselines in descending length.
+void staged_tables(int n_ant, int n_bl, int n_ubl, const std::vector<int2>& bl_ant,
+                   const std::vector<int>& bl_u, const std::vector<int4>& bl_pos,
+                   const std::vector<int>& u_off, std::vector<int2>& pack, std::vector<int2>& order) {
+  if (!staged_fits(n_ant, n_bl, n_ubl)) return;
+  for (int k = 0; k < n_bl; ++k) {
+    const bool neg = bl_u[k] < 0;
+    pack.push_back(pack_entry(bl_ant[k].x, bl_ant[k].y, neg ? ~bl_u[k] : bl_u[k], bl_pos[k].x, neg));
+  }
+  for (int u = 0; u < n_ubl; ++u) order.push_back(make_int2(u_off[u] | (u_off[u + 1] - u_off[u]) << 16, u));
+  std::stable_sort(order.begin(), order.end(), [](const int2& x, const int2& y) { return x.x >> 16 > y.x >> 16; });
 }
 
 // Sum of x[0..n) by one 1024-thread block in a fixed order: four independent
@@ -646,6 +864,34 @@ __device__ void KReduceGrads::run(const ReduceArgs& a, const Blk& B) {
   }
 }
 
+// Times per block such that n_freq blocks per slab of times fill `slots` resident
+// blocks in the least number of slice times (a block's start counts as one).
+static int times_per_block(int n_time, int n_freq, long slots) {
+  int best = n_time;
+  long least = -1;
+  for (int ts = n_time; ts >= 1; --ts) {
+    const long rounds = ceil_div(static_cast<long>(n_freq) * ceil_div(n_time, ts), slots);
+    const long cost = rounds * (ts + 1);
+    if (least < 0 || cost < least) {
+      least = cost;
+      best = ts;
+    }
+  }
+  return best;
+}
+
+template <int CAP>
+static void launch_staged(const vis_field* f, GainMode mode, GainArgs a, hipStream_t st) {
+  a.tslab = times_per_block(f->n_time, f->n_freq, static_cast<long>(f->n_cu) * (1024 / staged_threads(CAP)));
+  dim3 grid(f->n_freq, ceil_div(f->n_time, a.tslab));
+  if (mode == kGainChi2)
+    launch_k<KGainsStaged<CAP, kGainChi2>>(grid, 0, a, st, "k_gains");
+  else if (mode == kGainAdj)
+    launch_k<KGainsStaged<CAP, kGainAdj>>(grid, 0, a, st, "k_gains");
+  else
+    launch_k<KGainsStaged<CAP, kGainMap>>(grid, 0, a, st, "k_gains");
+}
+
 void launch_gains(const vis_field* f, GainMode mode, const float2* vu, const float2* gains,
                   const float2* din, float sigma_n, float2* vis_out, double* chi_part, float* gco,
                   float2* g_part, hipStream_t st) {
@@ -672,6 +918,8 @@ void launch_gains(const vis_field* f, GainMode mode, const float2* vu, const flo
   a.g_part = g_part;
   a.cplan = f->tab.cplan;
   a.gstride = f->gstride;
+  a.bl_pack = nullptr;
+  a.u_order = nullptr;
   a.split = fringe_split(f);
   const size_t lds = sizeof(float2) * (f->n_ant + 2 * f->n_ubl);
   BV_REQUIRE(lds <= 48 * 1024, VIS_EINVAL, "field too large for the gains pass LDS budget");
@@ -690,6 +938,15 @@ void launch_gains(const vis_field* f, GainMode mode, const float2* vu, const flo
       launch_k<KGains<true, kGainAdj>>(grid, lds_sorted, a, st, "k_gains");
     else
       launch_k<KGains<true, kGainMap>>(grid, lds_sorted, a, st, "k_gains");
+  } else if (mode != kGainFwd && staged_fits(f->n_ant, f->n_bl, f->n_ubl)) {
+    a.bl_pack = f->tab.bl_pack;
+    a.u_order = f->tab.u_order;
+    if (f->n_bl <= 2048)
+      launch_staged<2048>(f, mode, a, st);
+    else if (f->n_bl <= 4608)
+      launch_staged<4608>(f, mode, a, st);
+    else
+      launch_staged<kStagedMaxBaselines>(f, mode, a, st);
   } else {
     a.tslab = 1;
     dim3 grid(f->n_freq, f->n_time);

@@ -113,6 +113,8 @@ struct FieldTables {
   int* bl_u = nullptr;             // [n_bl] unique index, negative-encoded sign: u or ~u
   int4* bl_pos = nullptr;          // [n_bl] position of baseline k in u_list, and of its
                                    //   (k, role 0) and (k, role 1) entries in a_list
+  int2* bl_pack = nullptr;         // [n_bl] packed entries of the staged gains pass
+  int2* u_order = nullptr;         // [n_ubl] (first in u_list | length << 16, unique), longest first
   int* u_off = nullptr;            // [n_ubl + 1] CSR unique -> physical
   int* u_list = nullptr;           // [n_bl] (bl << 1) | (sign < 0)
   int* a_off = nullptr;            // [n_ant + 1] CSR antenna -> baselines
@@ -220,6 +222,15 @@ void launch_filter_cot(const vis_field* f, const vis_filter* flt, const Filtered
 enum GainMode { kGainFwd = 0, kGainChi2 = 1, kGainAdj = 2, kGainMap = 3 };
 void launch_map_finish(const vis_field* f, const vis_c64* gains, const float* fwhm, float* map,
                        float* weight, hipStream_t st);
+// Limits of the staged gains pass (its LDS and the bits of a packed entry) and
+// its tables (left empty beyond them).
+constexpr int kStagedMaxBaselines = 8192, kStagedMaxUnique = 512, kStagedMaxAntennas = 128;
+inline bool staged_fits(int n_ant, int n_bl, int n_ubl) {
+  return n_ant <= kStagedMaxAntennas && n_bl <= kStagedMaxBaselines && n_ubl <= kStagedMaxUnique;
+}
+void staged_tables(int n_ant, int n_bl, int n_ubl, const std::vector<int2>& bl_ant,
+                   const std::vector<int>& bl_u, const std::vector<int4>& bl_pos,
+                   const std::vector<int>& u_off, std::vector<int2>& pack, std::vector<int2>& order);
 // Where each entry of a (t, nu) slice of adjoint coefficients comes from
 // (the gains pass evaluates it from the slice's collapsed omega): see gains.hip.
 std::vector<int4> coef_plan(const std::vector<int>& ulut, int extent, int dtile, bool split,
