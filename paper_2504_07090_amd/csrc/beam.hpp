@@ -3,7 +3,7 @@
 // leaves out no other reads.
 #pragma once
 
-#include "common.hpp"
+#include "objects.hpp"
 
 namespace bv {
 
@@ -44,6 +44,23 @@ __device__ __forceinline__ int2 beam_range(const float* __restrict__ ex, int n, 
     r.y = base + 63 - __builtin_clzll(in);
   }
   return r;
+}
+
+// The chunks (64 slots each) within the beam of a field's widest channel, a
+// prefix of the field's chunks: the slots whose sky or dL/dI any kernel needs.
+struct BeamSlots {
+  const float* fwhm;
+  float sigr_max;
+  const float* chunk_ex;   // [nchunks], ascending
+  int nchunks;
+  __device__ __forceinline__ float cut() const { return beam_cut(fwhm[0] * sigr_max); }
+  __device__ __forceinline__ bool outside(int chunk) const { return chunk_ex[chunk] > cut(); }
+  __device__ __forceinline__ int slots(int lane) const {
+    return kChunk * beam_prefix<8>(chunk_ex, nchunks, cut(), lane);
+  }
+};
+inline BeamSlots beam_slots(const vis_field* f, const float* fwhm) {
+  return BeamSlots{fwhm, f->sigr_max, f->tab.chunk_ex, f->n_chunks};
 }
 
 }  // namespace bv

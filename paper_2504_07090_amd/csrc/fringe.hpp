@@ -379,10 +379,8 @@ __device__ __forceinline__ h8 tr_operand(const uint32_t* base, int pix0, int til
 // scale = 2^(13 - e) with dOmega max |I| < 2^e (B <= 1), so that every
 // |dOmega B I scale| < 2^13 and its FP16 lo part stays a normal number.
 struct ChanScaleArgs {
-  int nvp, nchunks;
-  float sigr_max;
-  const float* chunk_ex;
-  const float* fwhm;
+  int nvp;
+  BeamSlots beam;
   const float* img;
   float* part;   // [n_freq][kScaleParts]
 };
@@ -393,8 +391,7 @@ struct KChanScale {
   static __device__ void run(const ChanScaleArgs& a, const Blk& B) {
     __shared__ float red[4];
     // the slots the forward pass visits (the sky elsewhere is not current)
-    const int ns = kChunk * beam_prefix<8>(a.chunk_ex, a.nchunks, beam_cut(a.fwhm[0] * a.sigr_max),
-                                           threadIdx.x & 63);
+    const int ns = a.beam.slots(threadIdx.x & 63);
     const int seg = (ns + kScaleParts - 1) / kScaleParts;
     const int k0 = B.y * seg, k1 = min(ns, k0 + seg);
     const float* row = a.img + static_cast<size_t>(B.x) * a.nvp;
@@ -1292,7 +1289,7 @@ static void fwd_d(const vis_field* f, const float* img, const float* fwhm, float
   if (split) {
     ProfScope ps(&f->prof, "k_chan_scale", st);
     launch_k<KChanScale>(dim3(f->n_freq, kScaleParts), 0,
-                         ChanScaleArgs{f->nv_pad, f->n_chunks, f->sigr_max, T.chunk_ex, fwhm, img, f->scr.fscale}, st, "k_chan_scale");
+                         ChanScaleArgs{f->nv_pad, beam_slots(f, fwhm), img, f->scr.fscale}, st, "k_chan_scale");
   }
   ProfScope ps(&f->prof, "k_fringe_fwd", st);
   const FwdArgs a{f->n_freq, f->n_time, f->nv_pad, f->n_ubl, static_cast<float>(f->d_omega),

@@ -18,6 +18,7 @@
 // v_mfma_f32_16x16x32_{bf16,f16}: lane l holds A[l % 16][8 (l / 16) + j] and
 // B[8 (l / 16) + j][l % 16], j = 0..7; D as for the other 16x16 MFMAs.
 #include "batch.hpp"
+#include "beam.hpp"
 #include "objects.hpp"
 
 namespace bv {
@@ -154,6 +155,9 @@ __device__ void KSplitRows<Fmt>::run(const SplitRowsArgs& args_, const Blk& B_) 
 
 // part[split][f][k] = sum_{c in split} a[f][c] Y[vpix[k]][c]; tile 64 (f) x 64 (k),
 // K step 32.  A: split coefficient rows [nf_pad][kpad], zero beyond the modes.
+// The tiles outside the beam return at once (61 dishes, lmax 100, 64 channels:
+// 300 -> 105 us forward; the adjoint, whose K range shrinks with the prefix of
+// slots within the beam, 410 -> 134 us).
 struct SynthFwdSplitArgs {
   int nf;
   int nm;
@@ -167,6 +171,7 @@ struct SynthFwdSplitArgs {
   const unsigned short* Yl;
   const int* vpix;
   float* part;
+  BeamSlots beam;
 };
 
 template <class Fmt>
@@ -178,6 +183,7 @@ struct KSynthFwdSplit {
 
 template <class Fmt>
 __device__ void KSynthFwdSplit<Fmt>::run(const SynthFwdSplitArgs& args_, const Blk& B_) {
+  if (args_.beam.outside(B_.x)) return;   // 64 slots per tile: one chunk
   int nf = args_.nf;
   int nm = args_.nm;
   int nvp = args_.nvp;
@@ -265,7 +271,6 @@ struct SynthAdjSplitArgs {
   int nf;
   int nvp;
   int kpad;
-  int kps;
   const unsigned short* Dh;
   const unsigned short* Dl;
   const float* rscale;
@@ -273,6 +278,7 @@ struct SynthAdjSplitArgs {
   const unsigned short* Yl;
   const int* vpix;
   float* part;
+  BeamSlots beam;
 };
 
 template <class Fmt>
@@ -287,7 +293,6 @@ __device__ void KSynthAdjSplit<Fmt>::run(const SynthAdjSplitArgs& args_, const B
   int nf = args_.nf;
   int nvp = args_.nvp;
   int kpad = args_.kpad;
-  int kps = args_.kps;
   const unsigned short* __restrict__ Dh = args_.Dh;
   const unsigned short* __restrict__ Dl = args_.Dl;
   const float* __restrict__ rscale = args_.rscale;
@@ -300,7 +305,9 @@ __device__ void KSynthAdjSplit<Fmt>::run(const SynthAdjSplitArgs& args_, const B
   __shared__ __attribute__((aligned(16))) unsigned short Bh[2][64 * kHP], Bl[2][64 * kHP];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int n0 = B_.x * 64, m0 = B_.y * 64, split = B_.z;
-  const int kbeg = split * kps, kend = min(nvp, kbeg + kps);
+  // the slots within the beam, in equal shares of whole K steps
+  const int ns = args_.beam.slots(lane), kps = (ns / 32 + B_.nz - 1) / B_.nz * 32;
+  const int kbeg = min(ns, split * kps), kend = min(ns, kbeg + kps);
   const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
   const int lr = tid >> 2, lk = (tid & 3) * 8;      // A: row f, 8 pixels
   const int pq = (tid >> 5) * 4, cp = (tid & 31) * 2;   // B: 4 pixel rows, 2 modes
@@ -312,7 +319,7 @@ __device__ void KSynthAdjSplit<Fmt>::run(const SynthAdjSplitArgs& args_, const B
     for (int j = 0; j < 2; ++j) c1[i][j] = c2[i][j] = f4{0.f, 0.f, 0.f, 0.f};
   us8 rah, ral;
   unsigned rbh[4], rbl[4];   // modes (cp, cp + 1) of pixel rows pq .. pq + 3
-  // kbeg and kps are multiples of 32 and nvp of 64: steps stay inside the split
+  // kbeg and kps are multiples of 32 and ns of 64: steps stay inside the split
   const int ksteps = (kend - kbeg + 31) / 32;
   auto gload = [&](int k0) {
     rah = *reinterpret_cast<const us8*>(Dh + aoff + k0 + lk);
@@ -410,7 +417,8 @@ void split_rows(const vis_field* f, int ncols, int ld_src, int ld_dst, const flo
 }
 
 template <class Fmt>
-void fwd_split(const vis_field* f, const float* alm, float* dst, int nsplit, int kps, hipStream_t st) {
+void fwd_split(const vis_field* f, const float* alm, const float* fwhm, float* dst, int nsplit, int kps,
+               hipStream_t st) {
   const vis_basis* b = f->basis;
   const SplitY y = split_basis(f);
   const size_t plane = round_up(f->n_freq, 64) * static_cast<size_t>(b->kpad);
@@ -420,11 +428,11 @@ void fwd_split(const vis_field* f, const float* alm, float* dst, int nsplit, int
   dim3 grid(f->nv_pad / 64, ceil_div(f->n_freq, 64), nsplit);
   ProfScope ps(&f->prof, Fmt::kScaled ? "k_synth_fwd_fp16x3" : "k_synth_fwd_bf16x3", st);
   launch_k<KSynthFwdSplit<Fmt>>(grid, 0, SynthFwdSplitArgs{f->n_freq, f->n_modes, f->nv_pad, b->kpad, kps, ah, al,
-                                               f->scr.rscale, y.hi, y.lo, f->tab.vpix, dst}, st, "k_synth_fwd_split");
+                                               f->scr.rscale, y.hi, y.lo, f->tab.vpix, dst, beam_slots(f, fwhm)}, st, "k_synth_fwd_split");
 }
 
 template <class Fmt>
-void adj_split(const vis_field* f, const float* dimg, int kps, hipStream_t st) {
+void adj_split(const vis_field* f, const float* dimg, const float* fwhm, hipStream_t st) {
   const vis_basis* b = f->basis;
   const SplitY y = split_basis(f);
   const size_t plane = round_up(f->n_freq, 64) * static_cast<size_t>(f->nv_pad);
@@ -434,25 +442,25 @@ void adj_split(const vis_field* f, const float* dimg, int kps, hipStream_t st) {
   const int ncol = static_cast<int>(round_up(f->n_modes, 64));
   dim3 grid(ncol / 64, ceil_div(f->n_freq, 64), f->asplit);
   ProfScope ps(&f->prof, Fmt::kScaled ? "k_synth_adj_fp16x3" : "k_synth_adj_bf16x3", st);
-  launch_k<KSynthAdjSplit<Fmt>>(grid, 0, SynthAdjSplitArgs{f->n_freq, f->nv_pad, b->kpad, kps, dh, dl,
-                                               f->scr.rscale, y.hi, y.lo, f->tab.vpix, f->scr.a_part}, st, "k_synth_adj_split");
+  launch_k<KSynthAdjSplit<Fmt>>(grid, 0, SynthAdjSplitArgs{f->n_freq, f->nv_pad, b->kpad, dh, dl,
+                                               f->scr.rscale, y.hi, y.lo, f->tab.vpix, f->scr.a_part, beam_slots(f, fwhm)}, st, "k_synth_adj_split");
 }
 
 }  // namespace
 
 // Forward split synthesis into dst: nsplit partial planes [nsplit][n_freq][nv_pad]
 // of kps modes each (kps a multiple of 32); with nsplit == 1, dst is the sky itself.
-void launch_synth_fwd_split(const vis_field* f, const float* alm, float* dst, int nsplit, int kps,
-                            hipStream_t st) {
-  if (f->precision == VIS_BF16X3) fwd_split<Bf16Split>(f, alm, dst, nsplit, kps, st);
-  else fwd_split<F16Split>(f, alm, dst, nsplit, kps, st);
+void launch_synth_fwd_split(const vis_field* f, const float* alm, const float* fwhm, float* dst, int nsplit,
+                            int kps, hipStream_t st) {
+  if (f->precision == VIS_BF16X3) fwd_split<Bf16Split>(f, alm, fwhm, dst, nsplit, kps, st);
+  else fwd_split<F16Split>(f, alm, fwhm, dst, nsplit, kps, st);
 }
 
 // Adjoint split synthesis into the split-K partials a_part[asplit][n_freq][kpad]
-// (kps pixels each, a multiple of 32).
-void launch_synth_adj_split(const vis_field* f, const float* dimg, int kps, hipStream_t st) {
-  if (f->precision == VIS_BF16X3) adj_split<Bf16Split>(f, dimg, kps, st);
-  else adj_split<F16Split>(f, dimg, kps, st);
+// (equal shares of the pixels within the beam).
+void launch_synth_adj_split(const vis_field* f, const float* dimg, const float* fwhm, hipStream_t st) {
+  if (f->precision == VIS_BF16X3) adj_split<Bf16Split>(f, dimg, fwhm, st);
+  else adj_split<F16Split>(f, dimg, fwhm, st);
 }
 
 }  // namespace bv
