@@ -36,12 +36,18 @@ __device__ __forceinline__ int beam_prefix(const float* __restrict__ ex, int n, 
 // there is none); the same in every lane.
 __device__ __forceinline__ int2 beam_range(const float* __restrict__ ex, int n, float cut, int lane) {
   int2 r = make_int2(n, -1);
-  for (int base = 0; base < n; base += 64) {
-    const float e = ex[min(base + lane, n - 1)];
-    const unsigned long long in = __ballot(base + lane < n && !(e > cut));
-    if (in == 0) continue;
-    if (r.y < 0) r.x = base + __builtin_ctzll(in);
-    r.y = base + 63 - __builtin_clzll(in);
+  constexpr int kSeg = 2;   // 64-entry segments loaded at once
+  for (int base = 0; base < n; base += 64 * kSeg) {
+    float e[kSeg];
+#pragma unroll
+    for (int q = 0; q < kSeg; ++q) e[q] = ex[min(base + 64 * q + lane, n - 1)];
+#pragma unroll
+    for (int q = 0; q < kSeg; ++q) {
+      const unsigned long long in = __ballot(base + 64 * q + lane < n && !(e[q] > cut));
+      if (in == 0) continue;
+      if (r.y < 0) r.x = base + 64 * q + __builtin_ctzll(in);
+      r.y = base + 64 * q + 63 - __builtin_clzll(in);
+    }
   }
   return r;
 }
