@@ -158,9 +158,9 @@ vis_status chi2_filtered_and_grad(const vis_field* f, const vis_filter* flt, con
     forward_core(f, alm, fwhm, s);
     launch_gains(f, kGainFwd, f->scr.vu, reinterpret_cast<const float2*>(gains), nullptr, 0.f, w.m,
                  nullptr, nullptr, nullptr, s);
-    launch_filter_chi2(f, flt, reinterpret_cast<const float2*>(data), sigma_n, w, chi2, s);
-    if (!(grad_alm || grad_gains || grad_fwhm)) return;
-    launch_filter_cot(f, flt, w, s);
+    const bool grad = grad_alm || grad_gains || grad_fwhm;
+    launch_filter_chi2(f, flt, reinterpret_cast<const float2*>(data), sigma_n, w, grad, chi2, s);
+    if (!grad) return;
     launch_gains(f, kGainAdj, f->scr.vu, reinterpret_cast<const float2*>(gains), w.m, 0.f, nullptr,
                  nullptr, f->scr.gco, f->scr.g_part, s);
     adjoint_tail(f, fwhm, grad_alm, reinterpret_cast<float2*>(grad_gains), grad_fwhm, false, nullptr, s);

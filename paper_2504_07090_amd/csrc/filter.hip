@@ -16,6 +16,7 @@
 // lane j + 16 k, D[i][j] in lane j + 16 (i / 4), register i % 4).  The chi^2
 // terms are summed per wavefront in FP64 and totalled in a fixed order.
 #include <cmath>
+#include <type_traits>
 #include <vector>
 
 #include "objects.hpp"
@@ -87,8 +88,8 @@ static void build_filter(int n, const double* freq, double tau, double eps, std:
 }
 
 // --------------------------------------------------------------- kernels --
-// Both GEMMs stream the visibility-sized operands once, so they are bound by
-// HBM, not by the matrix cores: one wavefront per (time, 16 CT columns, 64
+// Beyond kFilterFusedRows channels the two GEMMs are launches of their own:
+// one wavefront per (time, 16 CT columns, 64
 // rows) keeps a 64 x 16 CT output block in registers (4 x CT tiles of
 // 16 x 16), reads each operand row segment once as 8-byte vectors, and loops
 // over all nf rows of the contraction, 16 per step with all the step's loads
@@ -198,6 +199,126 @@ k_filter_gemm(int nf, int nx, float inv_sig2, const float* __restrict__ F, const
   }
 }
 
+// Both GEMMs of 64 columns of one time in one block, for up to kFilterFusedRows
+// channels (a wave per 16 rows, at most 15 waves; the 64 columns of all rows fit
+// in 60 KB of LDS, two blocks to a CU).  The block loads d - m once, all loads in
+// flight together, into LDS; each wave forms its 16 rows of Rf from there, W
+// takes the place of d - m, and each wave forms 16 rows of the cotangent, which
+// overwrites the model in place (read before the first barrier, written after the
+// last).  part[time][column block] is the block's chi^2.  COT = false: chi^2 only.
+//
+// LDS rows are 64 floats, zero past nf and past the last column; the halves of
+// every second group of four rows are swapped, so that the rows a half-wave
+// touches at once (k and k + 4) lie in different banks.  MFMA step q of 16
+// contraction rows takes the rows k0 + 4 kk + q.
+//
+// Bound by the FP32 matrix cores and the loads before them.  61 dishes, 64
+// channels, 60 times (56 MB per visibility array): 70 us, against 83 us for a
+// launch each with one wave per 64 x 64 outputs, where W is written and read again.
+constexpr int kFilterFusedRows = 240, kFilterCols = 16 * kFilterColTiles;
+static_assert(kFilterCols == 64, "columns of a fused block");
+
+template <bool COT>
+__global__ void __launch_bounds__(4 * kFilterFusedRows)
+k_filter_fused(int nf, int nx, float inv_sig2, const float* __restrict__ F, const float* __restrict__ fft,
+               const float* __restrict__ d, float* m, double* __restrict__ part) {
+  typedef float f2 __attribute__((ext_vector_type(2)));
+  extern __shared__ float sh[];   // [nrow][64]
+  __shared__ double red[kFilterFusedRows / 16];
+  const int tid = threadIdx.x, lane = tid & 63, j = lane & 15, kk = lane >> 4;
+  const int wv = __builtin_amdgcn_readfirstlane(tid >> 6), nw = blockDim.x >> 6, nrow = 16 * nw;
+  const int x0 = blockIdx.x * kFilterCols, n0 = 16 * wv;
+  const size_t tb = static_cast<size_t>(blockIdx.y) * nf * nx;
+  auto at = [](int k, int c) { return 64 * k + (c ^ (32 * ((k >> 2) & 1))); };
+  {
+    // 32 threads per row, 2 nw rows per pass: eight passes
+    const int c = 2 * (tid & 31), xc = min(x0 + c, nx - 2);
+    f2 vd[8], vm[8];
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const size_t o = tb + static_cast<size_t>(min((tid >> 5) + 2 * nw * p, nf - 1)) * nx + xc;
+      vd[p] = *reinterpret_cast<const f2*>(d + o);
+      vm[p] = *reinterpret_cast<const f2*>(m + o);
+    }
+#pragma unroll
+    for (int p = 0; p < 8; ++p) {
+      const int k = (tid >> 5) + 2 * nw * p;
+      *reinterpret_cast<f2*>(sh + at(k, c)) = k < nf && x0 + c < nx ? vd[p] - vm[p] : f2{0.f, 0.f};
+    }
+  }
+  const int arow = min(n0 + j, nf - 1);   // rows past nf are not stored
+  f4 acc[4];
+  // acc = F (T: F^T) rows n0 .. n0 + 15 times the LDS rows
+  auto gemm = [&](auto transposed) {
+    constexpr bool T = decltype(transposed)::value;
+    auto filt = [&](int k0, float (&a)[4]) {   // any finite value where k >= nf: the operand's row is zero
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int k = min(k0 + 4 * kk + q, nf - 1);
+        a[q] = T ? F[static_cast<size_t>(k) * nf + arow] : F[static_cast<size_t>(arow) * nf + k];
+      }
+    };
+#pragma unroll
+    for (int c = 0; c < 4; ++c) acc[c] = f4{0.f, 0.f, 0.f, 0.f};
+    float a[4], an[4];
+    filt(0, a);
+    __syncthreads();   // the operand is in LDS
+    for (int k0 = 0; k0 < nrow; k0 += 16) {
+      filt(k0 + 16, an);
+      f2 b[4][2];
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int h = 0; h < 2; ++h)
+          b[q][h] = *reinterpret_cast<const f2*>(sh + at(k0 + 4 * kk + q, 32 * h + 2 * j));
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int c = 0; c < 4; ++c)
+          acc[c] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[q], b[q][c >> 1][c & 1], acc[c], 0, 0, 0);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) a[q] = an[q];
+    }
+  };
+  gemm(std::false_type{});
+  __syncthreads();   // d - m is read
+  double chi = 0.0;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int nu = n0 + 4 * kk + q;
+    const float w = nu < nf ? inv_sig2 / fft[nu] : 0.f;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const float v0 = nu < nf ? acc[2 * h][q] : 0.f, v1 = nu < nf ? acc[2 * h + 1][q] : 0.f;
+      chi += (static_cast<double>(v0) * v0 + static_cast<double>(v1) * v1) * w;
+      if (COT) *reinterpret_cast<f2*>(sh + at(nu, 32 * h + 2 * j)) = f2{v0 * w, v1 * w};
+    }
+  }
+  for (int o = 32; o >= 1; o >>= 1) chi += __shfl_xor(chi, o);
+  if (lane == 0) red[wv] = chi;
+  if (COT) {
+    gemm(std::true_type{});
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int nu = n0 + 4 * kk + q;
+      if (nu >= nf) continue;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int xc = x0 + 32 * h + 2 * j;   // even, and nx is even: the pair is whole or absent
+        if (xc < nx)
+          *reinterpret_cast<f2*>(m + tb + static_cast<size_t>(nu) * nx + xc) = f2{-2.0f * acc[2 * h][q], -2.0f * acc[2 * h + 1][q]};
+      }
+    }
+  } else {
+    __syncthreads();
+  }
+  if (tid == 0) {
+    double s = 0.0;
+    for (int w = 0; w < nw; ++w) s += red[w];
+    part[static_cast<size_t>(blockIdx.y) * gridDim.x + blockIdx.x] = s;
+  }
+}
+
 // out = sum of part[0..n) in FP64, one 1024-thread block, fixed order.
 __global__ void __launch_bounds__(1024) k_sum_f64(long n, const double* __restrict__ part, double* out) {
   __shared__ double red[16];
@@ -235,32 +356,42 @@ static void check_filter(const vis_field* f, const vis_filter* flt) {
 }
 
 void launch_filter_chi2(const vis_field* f, const vis_filter* flt, const float2* data, float sigma_n,
-                        const FilteredWork& w, double* chi2, hipStream_t st) {
+                        const FilteredWork& w, bool cot, double* chi2, hipStream_t st) {
   check_filter(f, flt);
-  const int nx = 2 * f->n_bl;
-  dim3 grid(ceil_div(nx, 16 * kFilterColTiles), ceil_div(f->n_freq, 64), f->n_time);
-  {
-    ProfScope ps(&f->prof, "k_filter_resid", st);
-    k_filter_gemm<true, kFilterColTiles><<<grid, 64, 0, st>>>(f->n_freq, nx, 1.0f / (sigma_n * sigma_n), flt->F, flt->fft,
-                                             reinterpret_cast<const float*>(data),
-                                             reinterpret_cast<const float*>(w.m),
-                                             reinterpret_cast<float*>(w.w), w.part);
-    check_launch("k_filter_resid");
+  const int nf = f->n_freq, nx = 2 * f->n_bl;
+  const float inv_sig2 = 1.0f / (sigma_n * sigma_n);
+  const float* d = reinterpret_cast<const float*>(data);
+  float* m = reinterpret_cast<float*>(w.m);
+  float* ww = reinterpret_cast<float*>(w.w);
+  const unsigned cols = ceil_div(nx, kFilterCols);
+  long nparts = w.nparts;
+  if (nf <= kFilterFusedRows) {
+    ProfScope ps(&f->prof, "k_filter_fused", st);
+    const unsigned waves = ceil_div(nf, 16);
+    const size_t lds = sizeof(float) * kFilterCols * 16 * waves;
+    const dim3 grid(cols, f->n_time);
+    nparts = static_cast<long>(cols) * f->n_time;   // at most the carved w.nparts
+    if (cot)
+      k_filter_fused<true><<<grid, 64 * waves, lds, st>>>(nf, nx, inv_sig2, flt->F, flt->fft, d, m, w.part);
+    else
+      k_filter_fused<false><<<grid, 64 * waves, lds, st>>>(nf, nx, inv_sig2, flt->F, flt->fft, d, m, w.part);
+    check_launch("k_filter_fused");
+  } else {
+    const dim3 grid(cols, ceil_div(nf, 64), f->n_time);
+    {
+      ProfScope ps(&f->prof, "k_filter_resid", st);
+      k_filter_gemm<true, kFilterColTiles><<<grid, 64, 0, st>>>(nf, nx, inv_sig2, flt->F, flt->fft, d, m, ww, w.part);
+      check_launch("k_filter_resid");
+    }
+    if (cot) {
+      ProfScope ps(&f->prof, "k_filter_cot", st);
+      k_filter_gemm<false, kFilterColTiles><<<grid, 64, 0, st>>>(nf, nx, 0.f, flt->F, nullptr, ww, nullptr, m, nullptr);
+      check_launch("k_filter_cot");
+    }
   }
   ProfScope ps(&f->prof, "k_sum_f64", st);
-  k_sum_f64<<<1, 1024, 0, st>>>(w.nparts, w.part, chi2);
+  k_sum_f64<<<1, 1024, 0, st>>>(nparts, w.part, chi2);
   check_launch("k_sum_f64");
-}
-
-void launch_filter_cot(const vis_field* f, const vis_filter* flt, const FilteredWork& w, hipStream_t st) {
-  check_filter(f, flt);
-  const int nx = 2 * f->n_bl;
-  dim3 grid(ceil_div(nx, 16 * kFilterColTiles), ceil_div(f->n_freq, 64), f->n_time);
-  ProfScope ps(&f->prof, "k_filter_cot", st);
-  k_filter_gemm<false, kFilterColTiles><<<grid, 64, 0, st>>>(f->n_freq, nx, 0.f, flt->F, nullptr,
-                                            reinterpret_cast<const float*>(w.w), nullptr,
-                                            reinterpret_cast<float*>(w.m), nullptr);
-  check_launch("k_filter_cot");
 }
 
 }  // namespace bv

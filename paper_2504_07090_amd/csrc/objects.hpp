@@ -204,7 +204,8 @@ inline int adj_coef_stride(int dtile, bool split) {
 
 // Delay-filtered likelihood: scratch carved from the caller's work buffer
 // (model / cotangent visibilities, the weighted filtered residual, chi^2
-// partials per wavefront), and the two GEMM passes over frequency.
+// partials per wavefront), and the two GEMM passes over frequency (with cot the
+// cotangent replaces the model in w.m).
 struct FilteredWork {
   float2* m = nullptr;      // [n_time][n_freq][n_bl] model, then the cotangent
   float2* w = nullptr;      // [n_time][n_freq][n_bl] F (d - m) / N~
@@ -214,8 +215,7 @@ struct FilteredWork {
 };
 FilteredWork carve_filtered_work(const vis_field* f, void* work, size_t bytes);
 void launch_filter_chi2(const vis_field* f, const vis_filter* flt, const float2* data, float sigma_n,
-                        const FilteredWork& w, double* chi2, hipStream_t st);
-void launch_filter_cot(const vis_field* f, const vis_filter* flt, const FilteredWork& w, hipStream_t st);
+                        const FilteredWork& w, bool cot, double* chi2, hipStream_t st);
 
 // kGainMap: the adjoint pass's collapse of a given cotangent onto the unique
 // baselines only (no gain gradient; the unique visibilities are not read).
