@@ -20,105 +20,125 @@ namespace bv {
 constexpr float kMapWeightFloor = 1e-6f;
 
 // w[f][k] = (A^H A)_pp for visible slot k; one wavefront per (64-pixel chunk,
-// channel).  Also clears the channel maxima that k_map_wmax raises.
+// kMapChan channels), which share the loads of theta^2 (one channel per wave read
+// the 12 MB table of 61 dishes and 60 times once per channel).  cmax[f][chunk] is
+// the chunk's largest weight.  Bound by the exponential's rate: 64 channels 26.5
+// -> 22.6 us.
+constexpr int kMapChan = 4;
+
 __global__ void __launch_bounds__(64)
 k_map_weight(int nf, int nvp, int nant, double d_omega, const float* __restrict__ sigr,
              const float* __restrict__ TH2, const int2* __restrict__ chunk_t,
              const float2* __restrict__ gains, const float* __restrict__ fwhm, float* __restrict__ w,
-             unsigned* __restrict__ wmax) {
-  const int chunk = blockIdx.x, f = blockIdx.y, lane = threadIdx.x;
-  if (chunk == 0 && lane == 0) wmax[f] = 0u;
-  const float sig = fwhm[0] * sigr[f];
-  const float kb = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
-  double s2 = 0.0, s4 = 0.0;
-  for (int a = lane; a < nant; a += 64) {
-    const float2 g = gains[static_cast<size_t>(f) * nant + a];
-    const double m2 = static_cast<double>(g.x) * g.x + static_cast<double>(g.y) * g.y;
-    s2 += m2;
-    s4 += m2 * m2;
+             float* __restrict__ cmax) {
+  const int chunk = blockIdx.x, f0 = blockIdx.y * kMapChan, lane = threadIdx.x;
+  float kb2[kMapChan];
+  double s2[kMapChan], s4[kMapChan];
+#pragma unroll
+  for (int c = 0; c < kMapChan; ++c) {
+    const float sig = fwhm[0] * sigr[min(f0 + c, nf - 1)];
+    const float kb = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
+    kb2[c] = -2.0f * kb;
+    s2[c] = s4[c] = 0.0;
   }
-  for (int o = 32; o >= 1; o >>= 1) {
-    s2 += __shfl_xor(s2, o);
-    s4 += __shfl_xor(s4, o);
-  }
-  const double sg = 0.5 * (s2 * s2 - s4);
+  for (int a = lane; a < nant; a += 64)
+#pragma unroll
+    for (int c = 0; c < kMapChan; ++c) {
+      const float2 g = gains[static_cast<size_t>(min(f0 + c, nf - 1)) * nant + a];
+      const double m2 = static_cast<double>(g.x) * g.x + static_cast<double>(g.y) * g.y;
+      s2[c] += m2;
+      s4[c] += m2 * m2;
+    }
   const int k = chunk * kChunk + lane;
   const int2 tr = chunk_t[chunk];
   // sum of B^2 = 2^(-2 theta^2 kb) over the visible times: four independent
   // partial sums so four loads are in flight; the hardware exponential
   // (a square below 2^-126 adds nothing to the weight)
-  float sb[4] = {0.f, 0.f, 0.f, 0.f};
+  float sb[kMapChan][4] = {};
   int t = tr.x;
   for (; t + 3 <= tr.y; t += 4) {
+    float th2[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) th2[q] = TH2[static_cast<size_t>(t + q) * nvp + k];
 #pragma unroll
     for (int q = 0; q < 4; ++q)
-      sb[q] += __builtin_amdgcn_exp2f(-2.0f * kb * TH2[static_cast<size_t>(t + q) * nvp + k]);
+#pragma unroll
+      for (int c = 0; c < kMapChan; ++c) sb[c][q] += __builtin_amdgcn_exp2f(kb2[c] * th2[q]);
   }
-  for (int q = 0; t <= tr.y; ++t, ++q)
-    sb[q] += __builtin_amdgcn_exp2f(-2.0f * kb * TH2[static_cast<size_t>(t) * nvp + k]);
-  const float sbt = (sb[0] + sb[1]) + (sb[2] + sb[3]);
-  w[static_cast<size_t>(f) * nvp + k] = static_cast<float>(d_omega * d_omega * sg * sbt);
+#pragma unroll
+  for (int q = 0; q < 3; ++q)
+    if (t + q <= tr.y) {
+      const float th2 = TH2[static_cast<size_t>(t + q) * nvp + k];
+#pragma unroll
+      for (int c = 0; c < kMapChan; ++c) sb[c][q] += __builtin_amdgcn_exp2f(kb2[c] * th2);
+    }
+#pragma unroll
+  for (int c = 0; c < kMapChan; ++c) {
+    if (f0 + c >= nf) break;   // uniform
+    double a2 = s2[c], a4 = s4[c];
+    for (int o = 32; o >= 1; o >>= 1) {
+      a2 += __shfl_xor(a2, o);
+      a4 += __shfl_xor(a4, o);
+    }
+    const float sbt = (sb[c][0] + sb[c][1]) + (sb[c][2] + sb[c][3]);
+    float wt = static_cast<float>(d_omega * d_omega * (0.5 * (a2 * a2 - a4)) * sbt);
+    w[static_cast<size_t>(f0 + c) * nvp + k] = wt;
+    for (int o = 32; o >= 1; o >>= 1) wt = fmaxf(wt, __shfl_xor(wt, o));
+    if (lane == 0) cmax[static_cast<size_t>(f0 + c) * gridDim.x + chunk] = wt;
+  }
 }
 
-// wmax[f] = max_k w[f][k] as the bits of a non-negative float (whose order
-// is that of the unsigned integers, so the atomic maximum of the slices is
-// exact and independent of their order); one 256-thread block per (channel,
-// slice of k).
+// map[f][p] = dimg[f][slot] / w[f][slot] where w >= floor * the channel's largest
+// weight, else 0.  Grid (ceil(npix / (256 kMapPix)), nf); every block takes the
+// maximum of its channel's chunks itself (a few values per thread), which a launch
+// between this one and the weights did before (10 us of the 61-dish map).
+constexpr int kMapPix = 4;
+
 __global__ void __launch_bounds__(256)
-k_map_wmax(int nvp, int nsplit, const float* __restrict__ w, unsigned* __restrict__ wmax) {
+k_map_finish(int npix, int nvp, int nchunks, const int* __restrict__ vidx, const float* __restrict__ dimg,
+             const float* __restrict__ w, const float* __restrict__ cmax, float* __restrict__ map,
+             float* __restrict__ weight) {
   __shared__ float red[4];
-  const int f = blockIdx.x, sl = blockIdx.y, tid = threadIdx.x;
-  const int per = (nvp + nsplit - 1) / nsplit, k0 = sl * per, k1 = min(nvp, k0 + per);
+  const int f = blockIdx.y, tid = threadIdx.x;
   float m = 0.f;
-  for (int k = k0 + tid; k < k1; k += 256) m = fmaxf(m, w[static_cast<size_t>(f) * nvp + k]);
+  for (int c = tid; c < nchunks; c += 256) m = fmaxf(m, cmax[static_cast<size_t>(f) * nchunks + c]);
   for (int o = 32; o >= 1; o >>= 1) m = fmaxf(m, __shfl_xor(m, o));
   if ((tid & 63) == 0) red[tid >> 6] = m;
   __syncthreads();
-  if (tid == 0) atomicMax(wmax + f, __float_as_uint(fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]))));
-}
-
-// map[f][p] = dimg[f][slot] / w[f][slot] where w >= floor * wmax[f], else 0.
-__global__ void __launch_bounds__(256)
-k_map_finish(int nf, int npix, int nvp, const int* __restrict__ vidx, const float* __restrict__ dimg,
-             const float* __restrict__ w, const unsigned* __restrict__ wmax, float* __restrict__ map,
-             float* __restrict__ weight) {
-  const long idx = static_cast<long>(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (idx >= static_cast<long>(nf) * npix) return;
-  const int f = static_cast<int>(idx / npix), p = static_cast<int>(idx - static_cast<long>(f) * npix);
-  const int slot = vidx[p];
-  float x = 0.f, wt = 0.f;
-  if (slot >= 0) {
-    const float wm = __uint_as_float(wmax[f]);
-    wt = w[static_cast<size_t>(f) * nvp + slot];
-    if (wt > 0.f && wt >= kMapWeightFloor * wm) x = dimg[static_cast<size_t>(f) * nvp + slot] / wt;
+  const float wm = fmaxf(fmaxf(red[0], red[1]), fmaxf(red[2], red[3]));
+#pragma unroll
+  for (int q = 0; q < kMapPix; ++q) {
+    const int p = (blockIdx.x * kMapPix + q) * 256 + tid;
+    if (p >= npix) break;
+    const int slot = vidx[p];
+    float x = 0.f, wt = 0.f;
+    if (slot >= 0) {
+      wt = w[static_cast<size_t>(f) * nvp + slot];
+      if (wt > 0.f && wt >= kMapWeightFloor * wm) x = dimg[static_cast<size_t>(f) * nvp + slot] / wt;
+    }
+    const size_t idx = static_cast<size_t>(f) * npix + p;
+    map[idx] = x;
+    if (weight != nullptr) weight[idx] = wt;
   }
-  map[idx] = x;
-  if (weight != nullptr) weight[idx] = wt;
 }
 
 void launch_map_finish(const vis_field* f, const vis_c64* gains, const float* fwhm, float* map,
                        float* weight, hipStream_t st) {
   // the sky scratch is free after the adjoint fringe pass: it holds the
-  // weights; the F-gradient partials (not needed here) the channel maxima
+  // weights; the F-gradient partials (not needed here) the chunks' maxima
   float* w = f->scr.img;
-  unsigned* wmax = reinterpret_cast<unsigned*>(f->scr.f_part);
+  float* cmax = f->scr.f_part;
   {
     ProfScope ps(&f->prof, "k_map_weight", st);
-    k_map_weight<<<dim3(f->n_chunks, f->n_freq), 64, 0, st>>>(
+    k_map_weight<<<dim3(f->n_chunks, ceil_div(f->n_freq, kMapChan)), 64, 0, st>>>(
         f->n_freq, f->nv_pad, f->n_ant, f->d_omega, f->tab.sigr, f->tab.th2,
-        f->tab.chunk_t, reinterpret_cast<const float2*>(gains), fwhm, w, wmax);
+        f->tab.chunk_t, reinterpret_cast<const float2*>(gains), fwhm, w, cmax);
     check_launch("k_map_weight");
   }
-  const int nsplit = std::max(1, std::min(16, f->n_chunks));
-  {
-    ProfScope ps(&f->prof, "k_map_wmax", st);
-    k_map_wmax<<<dim3(f->n_freq, nsplit), 256, 0, st>>>(f->nv_pad, nsplit, w, wmax);
-    check_launch("k_map_wmax");
-  }
-  const long n = static_cast<long>(f->n_freq) * f->basis->n_pix;
+  const int npix = f->basis->n_pix;
   ProfScope ps(&f->prof, "k_map_finish", st);
-  k_map_finish<<<ceil_div(n, 256), 256, 0, st>>>(f->n_freq, f->basis->n_pix, f->nv_pad, f->tab.vidx,
-                                                  f->scr.dimg, w, wmax, map, weight);
+  k_map_finish<<<dim3(ceil_div(npix, 256 * kMapPix), f->n_freq), 256, 0, st>>>(
+      npix, f->nv_pad, f->n_chunks, f->tab.vidx, f->scr.dimg, w, cmax, map, weight);
   check_launch("k_map_finish");
 }
 
