@@ -15,7 +15,10 @@ roofline's dominant kernel) and `ms_per_step_instrumented`.
 
 Headline value: fwd+adjoint complex MAC/s, one MAC being one term of the
 fringe sum for one (unique baseline, pixel above the horizon, channel, time),
-counted once for the forward and once for the adjoint contraction.
+counted once for the forward and once for the adjoint contraction.  The kernels
+leave out the terms whose beam weight is below 2^-40 of the largest at that time
+and channel (a 1e-12 part of a sum whose rounding is 1e-7): the value counts the
+terms that the sum has, the rooflines only those within the beam (`within_beam`).
 
 Serving (`serving` key): 64 concurrent chains on uneven hex fields
 (19-127 dishes, 16-128 channels, 10-120 times, lmax 30-100), one trajectory
@@ -48,6 +51,7 @@ if ROOT not in sys.path:
 
 PEAK = {"hbm_gbs": 8000.0, "fp32_mfma_tflops": 157.3, "bf16_mfma_tflops": 2500.0,
         "fp16_mfma_tflops": 2500.0}
+BEAM_BITS = 40   # kBeamBits of csrc/common.hpp
 EPS = 0.02   # leapfrog step in units of the diagonal-Hessian scale
 
 # HBM bytes per launch of the fringe kernels on this workload, from two
@@ -79,6 +83,19 @@ def measured_traffic(kernel):
     if b is None or TRAFFIC["sha256"] != sources_sha256(TRAFFIC["sources"]):
         return None
     return b
+
+
+def beam_fraction(cfg):
+    """Share of the fringe sum's terms (pixels above the horizon, over times and
+    channels) within the beam cut of the evaluation kernels."""
+    import numpy as np
+    from oracle import model, rime
+    from paper_2504_07090_amd import workload as w
+    of = model.Field(cfg)
+    th2 = np.where(of.up, np.arccos(np.clip(of.enu[..., 2], -1.0, 1.0)) ** 2, np.inf)
+    ex = np.sort((th2 - th2.min(axis=1, keepdims=True))[of.up])
+    sig = rime.beam_sigma(of.freqs, w.fwhm_ref_rad(cfg), cfg.beam_ref_hz)
+    return float(np.mean(np.searchsorted(ex, 2.0 * math.log(2.0) * BEAM_BITS * sig ** 2, "right")) / ex.size)
 
 
 def log(*a):
@@ -215,29 +232,29 @@ def extras_bench(vis, torch, fld, cfg, data, sigma, reps=20):
         vis.profile_enable(fld, False)
         return {k: v[1] / max(1, v[0]) for k, v in kt.items()}
 
-    # delay-filtered chi^2 + gradient: the filter GEMMs over frequency read the
-    # data and model and write the weighted residual (3 x 8 B per visibility),
-    # then read it and write the cotangent (2 x 8 B); 2 nf^2 flop per real
-    # column and time, 10.7 flop/B: HBM-bound
+    # delay-filtered chi^2 + gradient: the filter pass over frequency reads the
+    # data and model and writes the cotangent (3 x 8 B per visibility); two
+    # products of 2 nf^2 flop per real column and time
     ffn = lambda: vis.chi2_filtered_and_grad(fld, filt, data, sigma, alm, g, fw)
     ffn()
     ms_f = timed_reps(torch, ffn, reps)
     kf = kernel_times(ffn)
-    kr = kf.get("k_filter_resid", float("nan"))
-    roof_f = {"bound": "hbm", "kernel": "k_filter_resid", "kernel_ms": kr, "unit": "GB/s",
+    kr = kf.get("k_filter_fused", float("nan"))
+    roof_f = {"bound": "hbm", "kernel": "k_filter_fused", "kernel_ms": kr, "unit": "GB/s",
               "achieved": 3.0 * 8.0 * nvis / (kr * 1e-3) / 1e9, "peak": PEAK["hbm_gbs"]}
     roof_f["frac"] = roof_f["achieved"] / roof_f["peak"]
     out["delay_filtered_chi2_grad"] = {"ms": ms_f, "kernel_ms": kf, "roofline": roof_f,
-                                       "flop_per_launch": 2.0 * cfg.n_freq ** 2 * 2 * fld.n_bl * cfg.n_time}
+                                       "flop_per_launch": 4.0 * cfg.n_freq ** 2 * 2 * fld.n_bl * cfg.n_time}
     # map-making: collapse onto unique baselines, the adjoint fringe contraction
     # (same MAC count as the forward), the closed-form normalisation
+    inside = beam_fraction(cfg)
     mfn = lambda: vis.make_map(fld, data, g, fw)
     mfn()
     ms_m = timed_reps(torch, mfn, reps)
     km = kernel_times(mfn)
     ka = km.get("k_fringe_adj", float("nan"))
     roof_m = {"bound": "mfma", "kernel": "k_fringe_adj", "kernel_ms": ka, "unit": "TFLOP/s",
-              "achieved": 4.0 * fld.fwd_macs / (ka * 1e-3) / 1e12, "peak": PEAK["fp32_mfma_tflops"]}
+              "within_beam": inside, "achieved": 4.0 * inside * fld.fwd_macs / (ka * 1e-3) / 1e12, "peak": PEAK["fp32_mfma_tflops"]}
     roof_m["frac"] = roof_m["achieved"] / roof_m["peak"]
     out["map_making"] = {"ms": ms_m, "kernel_ms": km, "roofline": roof_m}
     # the oracle beside the GPU on the 16-dish workload (8 channels, 4 times)
@@ -479,10 +496,11 @@ def main():
     dom_ms = per[dom]
     nv = fld.info.n_pix_visible
     if dom.startswith("k_fringe"):
-        work = 4.0 * fld.fwd_macs            # 2 FMA per complex x real MAC
+        inside = beam_fraction(cfg)
+        work = 4.0 * inside * fld.fwd_macs   # 2 FMA per complex x real MAC
         # split-precision fields run both fringe GEMMs on FP16 MFMA
         roof = {"bound": "mfma", "peak": PEAK["fp32_mfma_tflops"] if prec == vis.VIS_FP32
-                else PEAK["fp16_mfma_tflops"]}
+                else PEAK["fp16_mfma_tflops"], "within_beam": inside}
     else:
         work = 2.0 * cfg.n_freq * nv * fld.n_modes
         roof = {"bound": "mfma", "peak": PEAK["fp32_mfma_tflops"] if prec == vis.VIS_FP32
