@@ -398,9 +398,10 @@ static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc*
         }
       }
     if (umax > 0.0) th2_near[t] = zenith_angle2(umax);
-    for (int p = 0; p < npix; ++p) {
-      const double u = U[static_cast<size_t>(t) * npix + p];
-      if (u > 0.0) near[p] = std::min(near[p], zenith_angle2(u) - th2_near[t]);
+    for (int p = 0; p < npix; ++p) {   // U becomes theta^2, -1 below the horizon
+      double& u = U[static_cast<size_t>(t) * npix + p];
+      u = u > 0.0 ? zenith_angle2(u) : -1.0;
+      if (u >= 0.0) near[p] = std::min(near[p], u - th2_near[t]);
     }
   }
   g.vpix = order_slots(basis, nt, first, last, nup, near);
@@ -427,8 +428,8 @@ static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc*
         const size_t w = static_cast<size_t>(t) * g.nv_pad + k;
         g.p1[w] = (e1[0] * E[o] + e1[1] * N[o]) / kCLight;
         g.p2[w] = (e2[0] * E[o] + e2[1] * N[o]) / kCLight;
-        if (U[o] > 0.0) {
-          const double th2 = zenith_angle2(U[o]);
+        if (U[o] >= 0.0) {
+          const double th2 = U[o];
           g.th2[w] = static_cast<float>(th2);
           th2_min = std::min(th2_min, th2);
           g.vis_pix_time += 1.0;
