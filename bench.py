@@ -64,8 +64,8 @@ EPS = 0.02   # leapfrog step in units of the diagonal-Hessian scale
 TRAFFIC = {
     "sources": ["paper_2504_07090_amd/csrc/fringe.hpp", "paper_2504_07090_amd/csrc/common.hpp",
                 "paper_2504_07090_amd/build.py"],
-    "sha256": "4a70a4f9bdfaf8239f323f3e473f87d5a2f626af547bdf4b32b4be21f49b12d5",
-    "bytes_per_launch": {"k_fringe_adj": 195683636, "k_fringe_fwd": 235222678},
+    "sha256": "0f3f0508ea77baad93c0bdfc2db4b8e2cc9299ceec8e6922f6db99d40d46a7b7",
+    "bytes_per_launch": {"k_fringe_adj": 81535693, "k_fringe_fwd": 27117442},
 }
 
 
