@@ -296,10 +296,15 @@ static std::vector<int> order_slots(const vis_basis* basis, int nt, const std::v
                                     const std::vector<double>& near) {
   const int npix = basis->n_pix, nphi = basis->nphi;
   std::vector<std::array<double, 3>> s(npix);
-  for (int p = 0; p < npix; ++p) {
-    const double z = -1.0 + (p / nphi + 0.5) * 2.0 / basis->nz, r = std::sqrt(std::max(0.0, 1.0 - z * z));
-    const double al = (p % nphi + 0.5) * 2.0 * kPi / nphi;
-    s[p] = {r * std::cos(al), r * std::sin(al), z};
+  std::vector<double> ca(nphi), sa(nphi);
+  for (int k = 0; k < nphi; ++k) {
+    const double al = (k + 0.5) * 2.0 * kPi / nphi;
+    ca[k] = std::cos(al);
+    sa[k] = std::sin(al);
+  }
+  for (int j = 0; j < basis->nz; ++j) {
+    const double z = -1.0 + (j + 0.5) * 2.0 / basis->nz, r = std::sqrt(std::max(0.0, 1.0 - z * z));
+    for (int k = 0; k < nphi; ++k) s[j * nphi + k] = {r * ca[k], r * sa[k], z};
   }
   std::vector<int> up;
   for (int p = 0; p < npix; ++p)
