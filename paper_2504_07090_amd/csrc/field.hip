@@ -253,27 +253,31 @@ static double zenith_angle2(double u) {
   return th * th;
 }
 
+// Unit vector and index of a pixel.
+struct SkyPix {
+  std::array<double, 3> s;
+  int p;
+};
 // Splits pix[lo, hi) into chunks of kChunk pixels that are compact on the sky:
 // halves at a multiple of kChunk along the axis (of the unit vectors) in which
 // the set extends furthest, until one chunk is left.
-static void bisect_chunks(std::vector<int>& pix, size_t lo, size_t hi,
-                          const std::vector<std::array<double, 3>>& s) {
+static void bisect_chunks(std::vector<SkyPix>& pix, size_t lo, size_t hi) {
   if (hi - lo <= static_cast<size_t>(kChunk)) return;
-  std::array<double, 3> mn = s[pix[lo]], mx = mn;
+  std::array<double, 3> mn = pix[lo].s, mx = mn;
   for (size_t i = lo; i < hi; ++i)
     for (int a = 0; a < 3; ++a) {
-      mn[a] = std::min(mn[a], s[pix[i]][a]);
-      mx[a] = std::max(mx[a], s[pix[i]][a]);
+      mn[a] = std::min(mn[a], pix[i].s[a]);
+      mx[a] = std::max(mx[a], pix[i].s[a]);
     }
   int ax = 0;
   for (int a = 1; a < 3; ++a)
     if (mx[a] - mn[a] > mx[ax] - mn[ax]) ax = a;
   const size_t nch = (hi - lo + kChunk - 1) / kChunk, mid = lo + (nch / 2) * kChunk;
-  std::nth_element(pix.begin() + lo, pix.begin() + mid, pix.begin() + hi, [&](int a, int b) {
-    return s[a][ax] != s[b][ax] ? s[a][ax] < s[b][ax] : a < b;
+  std::nth_element(pix.begin() + lo, pix.begin() + mid, pix.begin() + hi, [&](const SkyPix& a, const SkyPix& b) {
+    return a.s[ax] != b.s[ax] ? a.s[ax] < b.s[ax] : a.p < b.p;
   });
-  bisect_chunks(pix, lo, mid, s);
-  bisect_chunks(pix, mid, hi, s);
+  bisect_chunks(pix, lo, mid);
+  bisect_chunks(pix, mid, hi);
 }
 
 // The pixel of every visible slot.  A chunk of kChunk slots is visited, per
@@ -295,17 +299,25 @@ static std::vector<int> order_slots(const vis_basis* basis, int nt, const std::v
                                     const std::vector<int>& last, const std::vector<int>& nup,
                                     const std::vector<double>& near) {
   const int npix = basis->n_pix, nphi = basis->nphi;
-  std::vector<std::array<double, 3>> s(npix);
   std::vector<double> ca(nphi), sa(nphi);
   for (int k = 0; k < nphi; ++k) {
     const double al = (k + 0.5) * 2.0 * kPi / nphi;
     ca[k] = std::cos(al);
     sa[k] = std::sin(al);
   }
-  for (int j = 0; j < basis->nz; ++j) {
-    const double z = -1.0 + (j + 0.5) * 2.0 / basis->nz, r = std::sqrt(std::max(0.0, 1.0 - z * z));
-    for (int k = 0; k < nphi; ++k) s[j * nphi + k] = {r * ca[k], r * sa[k], z};
-  }
+  auto bisected = [&](const std::vector<int>& in) {
+    std::vector<SkyPix> sp;
+    sp.reserve(in.size());
+    for (int p : in) {
+      const double z = -1.0 + (p / nphi + 0.5) * 2.0 / basis->nz, r = std::sqrt(std::max(0.0, 1.0 - z * z));
+      sp.push_back({{r * ca[p % nphi], r * sa[p % nphi], z}, p});
+    }
+    bisect_chunks(sp, 0, sp.size());
+    std::vector<int> out;
+    out.reserve(sp.size());
+    for (const SkyPix& v : sp) out.push_back(v.p);
+    return out;
+  };
   std::vector<int> up;
   for (int p = 0; p < npix; ++p)
     if (nup[p] > 0) up.push_back(p);
@@ -316,12 +328,11 @@ static std::vector<int> order_slots(const vis_basis* basis, int nt, const std::v
   const size_t n_always = std::count_if(up.begin(), up.end(), [&](int p) { return nup[p] == nt; });
   std::vector<int> pix;
   if (2 * n_always < up.size()) {
-    pix = up;
-    bisect_chunks(pix, 0, pix.size(), s);
+    pix = bisected(up);
   } else {
     std::vector<int> rest;
     for (int p : up) (nup[p] == nt ? pix : rest).push_back(p);
-    bisect_chunks(pix, 0, pix.size(), s);
+    pix = bisected(pix);
     std::sort(rest.begin(), rest.end(), [&](int a, int b) {
       return first[a] != first[b] ? first[a] < first[b] : last[a] != last[b] ? last[a] < last[b] : a < b;
     });
