@@ -1,6 +1,6 @@
 // Beam cut of the evaluation kernels (kBeamBits): every kernel of a field
-// derives the same cut from the beam width on the device, so that what one
-// leaves out no other reads.
+// derives the same cut from the beam width on the device and the field's
+// cut_sig2, so that what one leaves out no other reads.
 #pragma once
 
 #include "objects.hpp"
@@ -8,9 +8,7 @@
 namespace bv {
 
 // Excess theta^2 beyond which a beam of width sig is cut.
-__device__ __forceinline__ float beam_cut(float sig) {
-  return kBeamBits * 2.0f * static_cast<float>(kLn2) * sig * sig;
-}
+__device__ __forceinline__ float beam_cut(float cut_sig2, float sig) { return cut_sig2 * sig * sig; }
 
 // Number of leading entries of an ascending excess list up to `cut`; the same
 // in every lane.  SEG 64-entry segments load at once.  An undefined cut (NaN)
@@ -56,17 +54,17 @@ __device__ __forceinline__ int2 beam_range(const float* __restrict__ ex, int n, 
 // prefix of the field's chunks: the slots whose sky or dL/dI any kernel needs.
 struct BeamSlots {
   const float* fwhm;
-  float sigr_max;
+  float sigr_max, cut_sig2;
   const float* chunk_ex;   // [nchunks], ascending
   int nchunks;
-  __device__ __forceinline__ float cut() const { return beam_cut(fwhm[0] * sigr_max); }
+  __device__ __forceinline__ float cut() const { return beam_cut(cut_sig2, fwhm[0] * sigr_max); }
   __device__ __forceinline__ bool outside(int chunk) const { return chunk_ex[chunk] > cut(); }
   __device__ __forceinline__ int slots(int lane) const {
     return kChunk * beam_prefix<8>(chunk_ex, nchunks, cut(), lane);
   }
 };
 inline BeamSlots beam_slots(const vis_field* f, const float* fwhm) {
-  return BeamSlots{fwhm, f->sigr_max, f->tab.chunk_ex, f->n_chunks};
+  return BeamSlots{fwhm, f->sigr_max, f->cut_sig2, f->tab.chunk_ex, f->n_chunks};
 }
 
 }  // namespace bv

@@ -99,13 +99,24 @@ constexpr double kLn2 = 0.69314718055994531;
 
 constexpr int kChunk = 64;        // pixels per fringe chunk (one wavefront)
 // Beam cut of the fringe passes, in powers of two: a chunk whose beam at its
-// nearest pixel is below 2^-40 of the beam at the pixel nearest the zenith, at
-// that time and channel, is not visited.  The weight of a Gaussian beam beyond
-// the radius at which it falls to b is b of its total, so what is left out is
-// 2^-40 of the sum's weight, 2^-16 of one FP32 rounding of it; the sky itself
-// carries 2^-24 of its largest value in rounding errors at every pixel, beam
-// centre included, so no sky makes the omitted terms count.
-constexpr float kBeamBits = 40.0f;
+// nearest pixel is below 2^-bits of the beam at the pixel nearest the zenith, at
+// that time and channel, is not visited.  A field takes kBeamBits or more
+// (beam_bits in field.hip).
+//
+// The weight of a Gaussian beam beyond the radius at which it falls to b is b of
+// its total, so 40 bits leave out 2^-40 of the weight of a sky with power near
+// the beam centre.  A harmonic of degree l and order |m| near l has next to none
+// there at high latitudes: it falls as cos^|m|(dec) towards the poles, each value
+// exact relative to itself, and what the beam leaves of it comes from its
+// equator side.  So the cut also keeps every pixel whose beam times
+// cos^lmax(dec) is within 2^-kModeBits of the largest such product: what is left
+// out of any mode is then below FP32's rounding of its largest term (computed in
+// FP64 for l = |m| up to 150, latitudes -30.7 to -90 deg, beams of 4 to 35 deg, 61
+// dishes: at most 4e-8 of the visibilities, normwise; with 40 bits alone 6e-9 at
+// -30.7 deg and l = 100, 2e-2 at -60 deg, all of it at -90 deg).  At -30.7 deg
+// that takes no more than the 40 bits up to lmax 110.  Beyond kMaxBeamBits the
+// beam itself is 0 in FP32.
+constexpr float kBeamBits = 40.0f, kModeBits = 24.0f, kMaxBeamBits = 150.0f;
 constexpr int kScaleParts = 16;   // row segments of the split forward's sky maxima
 constexpr int kMaxExtent = 16;    // max |lattice difference| supported
 constexpr int kSepPad = 4;        // zero azimuthal columns on each side of the separable T table

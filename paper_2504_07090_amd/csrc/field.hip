@@ -209,6 +209,7 @@ struct HostGeometry {
   std::vector<int> tchunk_off, tchunk, ctime_off, ctime;
   std::vector<float> tchunk_ex, ctime_ex, chunk_ex;   // chunk_ex: a chunk's smallest ctime_ex
   double vis_pix_time = 0.0;             // sum over t of visible pixel count
+  double beam_bits = kBeamBits;          // of the beam cut
 };
 
 static void validate_field(const vis_basis* basis, const vis_field_desc* d) {
@@ -354,6 +355,36 @@ static std::vector<int> order_slots(const vis_basis* basis, int nt, const std::v
   return out;
 }
 
+// Bits of the beam cut that keep, at one time and for beams of any width, every
+// pixel whose beam times cos^lmax(dec) is within 2^-kModeBits of the largest
+// such product over the pixels up.  near[j]: the smallest theta^2 of ring j
+// (kBelowHorizon: none up), c[j] = -lmax log2 cos(dec_j), u the minimum of near.
+// In bits, a pixel of ring j then has f = kb theta^2 + c[j], kb = 1 / (2 ln 2
+// sigma^2), and is kept if f <= min f + kModeBits; the excess kb (theta^2 - u) of
+// any such pixel is at most min f + kModeBits - c[j] - kb u.  A mode of lower
+// order m is the same problem at kb lmax / m with all but the kModeBits scaled by
+// m / lmax, so the maximum over the widths (in half octaves, over which it
+// changes by about half a bit) covers every order.
+static double mode_bits(const std::vector<double>& near, const std::vector<double>& c, double u) {
+  int lo = 0, hi = static_cast<int>(near.size());
+  const double c_u = c[std::min_element(near.begin(), near.end()) - near.begin()];
+  if (c_u + kModeBits <= kBeamBits) return kBeamBits;   // min f <= kb u + c_u, c >= 0
+  double best = kBeamBits;
+  // below 2^4 the horizon is within 40 bits
+  for (double kb = 16.0; best < kMaxBeamBits; kb *= std::sqrt(2.0)) {
+    // rings beyond `far` are not kept, nor at a larger kb
+    const double far = u + (c_u + kModeBits) / kb;
+    while (near[lo] > far) ++lo;
+    while (near[hi - 1] > far) --hi;
+    if (hi - lo == 1) break;   // the nearest ring alone: at most kModeBits
+    double fmin = kb * u + c_u;
+    for (int j = lo; j < hi; ++j) fmin = std::min(fmin, kb * near[j] + c[j]);
+    for (int j = lo; j < hi; ++j)
+      if (kb * near[j] + c[j] <= fmin + kModeBits) best = std::max(best, fmin + kModeBits - c[j] - kb * u);
+  }
+  return std::min<double>(best, kMaxBeamBits);
+}
+
 static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc* d) {
   HostGeometry g;
   const int na = d->n_ant;
@@ -392,6 +423,8 @@ static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc*
   // near[p]: the smallest theta^2(p, t) - min_q theta^2(q, t) over the times at
   // which p is up; th2_near[t]: that minimum, the pixel nearest the zenith
   std::vector<double> th2_near(nt, kBelowHorizon), near(npix, kBelowHorizon);
+  std::vector<double> cmode(nz), uring(nz), ring_near(nz);
+  for (int j = 0; j < nz; ++j) cmode[j] = -d->lmax * std::log2(cring[j]);
   for (int t = 0; t < nt; ++t) {
     for (int k = 0; k < nphi; ++k) {
       const double h = d->lst_rad[t] - (k + 0.5) * 2.0 * kPi / nphi;
@@ -399,21 +432,28 @@ static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc*
       sha[k] = std::sin(h);
     }
     double umax = -1.0;
-    for (int j = 0; j < nz; ++j)
+    for (int j = 0; j < nz; ++j) {
+      uring[j] = -1.0;
       for (int k = 0; k < nphi; ++k) {
         const int p = j * nphi + k;
         const size_t o = static_cast<size_t>(t) * npix + p;
         E[o] = -cring[j] * sha[k];
         N[o] = cphi * zring[j] - sphi * cring[j] * cha[k];
         U[o] = sphi * zring[j] + cphi * cring[j] * cha[k];
-        umax = std::max(umax, U[o]);
+        uring[j] = std::max(uring[j], U[o]);
         if (U[o] > 0.0) {
           if (first[p] < 0) first[p] = t;
           last[p] = t;
           ++nup[p];
         }
       }
-    if (umax > 0.0) th2_near[t] = zenith_angle2(umax);
+      umax = std::max(umax, uring[j]);
+    }
+    if (umax > 0.0) {
+      th2_near[t] = zenith_angle2(umax);
+      for (int j = 0; j < nz; ++j) ring_near[j] = uring[j] > 0.0 ? zenith_angle2(uring[j]) : kBelowHorizon;
+      g.beam_bits = std::max(g.beam_bits, mode_bits(ring_near, cmode, th2_near[t]));
+    }
     for (int p = 0; p < npix; ++p) {   // U becomes theta^2, -1 below the horizon
       double& u = U[static_cast<size_t>(t) * npix + p];
       u = u > 0.0 ? zenith_angle2(u) : -1.0;
@@ -774,6 +814,7 @@ vis_status vis_field_create(const vis_basis* basis, const vis_field_desc* desc, 
       sigr[k] = static_cast<float>(desc->beam_ref_hz / freq[k] * kFwhmToSigma);
       f->sigr_max = std::max(f->sigr_max, sigr[k]);
     }
+    f->cut_sig2 = static_cast<float>(g.beam_bits) * 2.0f * static_cast<float>(kLn2);
     {
       // |p| <= |e| / c for every direction, |y| <= 1/2
       const double* e1 = desc->lattice_e1_m;

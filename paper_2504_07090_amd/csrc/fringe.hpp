@@ -456,7 +456,7 @@ constexpr int kFwdWaves = 4;
 
 struct FwdArgs {
   int nf, nt, nvp, nubl;
-  float d_omega;
+  float d_omega, cut_sig2;
   const float* dnu;
   const float* sigr;
   const float2* Q1;
@@ -542,7 +542,7 @@ __device__ void KFringeFwd<D, SPLIT, WRAP>::run(const FwdArgs& args, const Blk& 
     csc[c] = SPLIT ? chan_scale(args.cscale, fl, d_omega) : 1.0f;   // power of two
     const float sig = fwhm[0] * args.sigr[fl];
     kb[c] = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
-    cut = c == 0 ? beam_cut(sig) : fmaxf(cut, beam_cut(sig));
+    cut = c == 0 ? beam_cut(args.cut_sig2, sig) : fmaxf(cut, beam_cut(args.cut_sig2, sig));
     imf[c] = img + static_cast<size_t>(fl) * nvp;
   }
 
@@ -905,7 +905,7 @@ template <int RT> struct AdjCoef<RT, true> { h8 ga[RT][RT]; h4 gb[RT][RT]; };
 
 struct AdjArgs {
   int nf, nt, nvp, nchunks, gstride;
-  float d_omega;
+  float d_omega, cut_sig2;
   const float* dnu;
   const float* sigr;
   const float2* Q1;
@@ -990,7 +990,7 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
     }
   };
   const float fw = fwhm[0];
-  const float cut_w = beam_cut(fw * args.sigr_max);   // the field's widest channel
+  const float cut_w = beam_cut(args.cut_sig2, fw * args.sigr_max);   // the field's widest channel
   // Items are (chunk, channel group) pairs, chunk-major.  The chunks come
   // sorted by their nearest approach to the beam centre: those within the beam
   // of the field's widest channel are a prefix, the longest time loops start
@@ -1030,7 +1030,7 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
     dnu[c] = args.dnu[fch[c]];
     const float sig = fw * args.sigr[fch[c]];
     kb[c] = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
-    cut = c == 0 ? beam_cut(sig) : fmaxf(cut, beam_cut(sig));
+    cut = c == 0 ? beam_cut(args.cut_sig2, sig) : fmaxf(cut, beam_cut(args.cut_sig2, sig));
     acc_i[c] = acc_f[c] = 0.f;
   }
   // NCH > 1: the tile's row block r / 2D and column block belong to one
@@ -1310,7 +1310,7 @@ static void fwd_d(const vis_field* f, const float* img, const float* fwhm, float
   }
   ProfScope ps(&f->prof, "k_fringe_fwd", st);
   const FwdArgs a{f->n_freq, f->n_time, f->nv_pad, f->n_ubl, static_cast<float>(f->d_omega),
-                  T.dnu, T.sigr, T.q1, T.q2, T.th2, T.tchunk_off, T.tchunk, T.tchunk_ex, T.ubl_nm,
+                  f->cut_sig2, T.dnu, T.sigr, T.q1, T.q2, T.th2, T.tchunk_off, T.tchunk, T.tchunk_ex, T.ubl_nm,
                   img, fwhm, vu, split ? f->scr.fscale : nullptr};
   const bool wrap = f->max_turns > kMaxTurns;
   auto launch = [&](auto k) { launch_k<typename decltype(k)::Kernel>(dim3(nblk), 0, a, st, "k_fringe_fwd"); };
@@ -1333,7 +1333,7 @@ static void adj_d(const vis_field* f, const float* img, const float* fwhm, const
   BV_REQUIRE(f->dtile == D, VIS_EINVAL, "internal: adjoint tile mismatch");
   BV_REQUIRE((dimg == nullptr) != (dfull == nullptr), VIS_EINVAL, "internal: one adjoint output");
   const AdjArgs a{f->n_freq, f->n_time, f->nv_pad, f->n_chunks, f->gstride,
-                  static_cast<float>(f->d_omega), T.dnu, T.sigr, T.q1, T.q2, T.th2,
+                  static_cast<float>(f->d_omega), f->cut_sig2, T.dnu, T.sigr, T.q1, T.q2, T.th2,
                   T.chunk_ex, f->sigr_max, split_chunks,
                   static_cast<unsigned>(((1ull << 32) + nfg - 1) / nfg), T.ctime_off, T.ctime, T.ctime_ex, img, fwhm, gco, gco, dimg, f_part, dfull, T.sep_voff, f->nv,
                   f->basis->nphi_b};

@@ -157,6 +157,7 @@ struct vis_field {
   double d_omega = 0.0;
   double beam_ref_hz = 150e6;
   float sigr_max = 0.f;            // largest tab.sigr: the widest beam of the field
+  float cut_sig2 = 0.f;            // beam cut: excess theta^2 over sigma^2, 2 ln 2 times its bits
   float max_turns = 0.f;           // bound on |y + dnu p| of the phase tables, cycles
   double fwd_macs = 0.0;
   bv::FieldTables tab;

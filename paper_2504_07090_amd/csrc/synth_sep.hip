@@ -70,9 +70,9 @@ static_assert(kSepStep == 4 * kSepBatch, "K covered per batch");
 // What the stages need to find the rings and batches within the beam.
 struct SepBeam {
   const float* fwhm;
-  float sigr_max;
+  float sigr_max, cut_sig2;
   const float* ring_ex;   // [nz]
-  __device__ float cut() const { return beam_cut(fwhm[0] * sigr_max); }
+  __device__ float cut() const { return beam_cut(cut_sig2, fwhm[0] * sigr_max); }
 };
 
 // G[j][c][nu] = sum_{l=|m|}^{lmax} lambda_l|m|(z_j) a[nu][l^2 + l + m],  c = m + lmax,
@@ -514,7 +514,7 @@ void launch_synth_fwd_sep(const vis_field* f, const float* alm, const float* fwh
   BV_REQUIRE(b->sep_lam != nullptr, VIS_EINVAL, "basis has no separable factor tables");
   const int L = f->lmax;
   const int toff = b->lmax + kSepPad - L;   // T column of c = 0 (m = -L)
-  const SepBeam beam{fwhm, f->sigr_max, f->tab.sep_ring_ex};
+  const SepBeam beam{fwhm, f->sigr_max, f->cut_sig2, f->tab.sep_ring_ex};
   {
     ProfScope ps(&f->prof, "k_sep_leg_fwd", st);
     launch_k<KSepLegFwd>(dim3(L + 1, ceil_div(f->n_freq, 16)), 0,
@@ -535,7 +535,7 @@ void launch_synth_adj_sep(const vis_field* f, const float* fwhm, float* grad_alm
   BV_REQUIRE(b->sep_lam != nullptr, VIS_EINVAL, "basis has no separable factor tables");
   const int L = f->lmax;
   const int toff = b->lmax + kSepPad - L;
-  const SepBeam beam{fwhm, f->sigr_max, f->tab.sep_ring_ex};
+  const SepBeam beam{fwhm, f->sigr_max, f->cut_sig2, f->tab.sep_ring_ex};
   {
     ProfScope ps(&f->prof, "k_sep_az_adj", st);
     const int ctiles = ceil_div(2 * L + 1, 32), per_ring = ctiles * ceil_div(f->n_freq, 32);
