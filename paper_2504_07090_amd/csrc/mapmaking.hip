@@ -22,12 +22,14 @@ constexpr float kMapWeightFloor = 1e-6f;
 // w[f][k] = (A^H A)_pp for visible slot k; one wavefront per (64-pixel chunk,
 // kMapChan channels), which share the loads of theta^2 (one channel per wave read
 // the 12 MB table of 61 dishes and 60 times once per channel).  cmax[f][chunk] is
-// the chunk's largest weight.  Bound by the exponential's rate: 64 channels 26.5
-// -> 22.6 us.
+// the chunk's largest weight.  Slots without a pixel (k >= nv) get 0: w is the
+// sky scratch, whose padding must stay finite, and an undefined width or gain
+// makes every weight NaN.  Bound by the exponential's rate: 64 channels 26.5 ->
+// 22.6 us.
 constexpr int kMapChan = 4;
 
 __global__ void __launch_bounds__(64)
-k_map_weight(int nf, int nvp, int nant, double d_omega, const float* __restrict__ sigr,
+k_map_weight(int nf, int nv, int nvp, int nant, double d_omega, const float* __restrict__ sigr,
              const float* __restrict__ TH2, const int2* __restrict__ chunk_t,
              const float2* __restrict__ gains, const float* __restrict__ fwhm, float* __restrict__ w,
              float* __restrict__ cmax) {
@@ -81,7 +83,7 @@ k_map_weight(int nf, int nvp, int nant, double d_omega, const float* __restrict_
       a4 += __shfl_xor(a4, o);
     }
     const float sbt = (sb[c][0] + sb[c][1]) + (sb[c][2] + sb[c][3]);
-    float wt = static_cast<float>(d_omega * d_omega * (0.5 * (a2 * a2 - a4)) * sbt);
+    float wt = k < nv ? static_cast<float>(d_omega * d_omega * (0.5 * (a2 * a2 - a4)) * sbt) : 0.f;
     w[static_cast<size_t>(f0 + c) * nvp + k] = wt;
     for (int o = 32; o >= 1; o >>= 1) wt = fmaxf(wt, __shfl_xor(wt, o));
     if (lane == 0) cmax[static_cast<size_t>(f0 + c) * gridDim.x + chunk] = wt;
@@ -131,7 +133,7 @@ void launch_map_finish(const vis_field* f, const vis_c64* gains, const float* fw
   {
     ProfScope ps(&f->prof, "k_map_weight", st);
     k_map_weight<<<dim3(f->n_chunks, ceil_div(f->n_freq, kMapChan)), 64, 0, st>>>(
-        f->n_freq, f->nv_pad, f->n_ant, f->d_omega, f->tab.sigr, f->tab.th2,
+        f->n_freq, f->nv, f->nv_pad, f->n_ant, f->d_omega, f->tab.sigr, f->tab.th2,
         f->tab.chunk_t, reinterpret_cast<const float2*>(gains), fwhm, w, cmax);
     check_launch("k_map_weight");
   }
