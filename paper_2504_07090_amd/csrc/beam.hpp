@@ -7,6 +7,14 @@
 
 namespace bv {
 
+// kb of a beam of width sig, B = 2^(-theta^2 kb).  Never below 1e-27, so that the
+// marker of a pixel below the horizon or of a slot without one (kBelowHorizon)
+// has beam 0 at any width, and theta^2 < pi^2 / 4 beam 1; an undefined width stays so.
+__device__ __forceinline__ float beam_kb(float sig) {
+  const float kb = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
+  return kb < 1e-27f ? 1e-27f : kb;
+}
+
 // Excess theta^2 beyond which a beam of width sig is cut.
 __device__ __forceinline__ float beam_cut(float cut_sig2, float sig) { return cut_sig2 * sig * sig; }
 

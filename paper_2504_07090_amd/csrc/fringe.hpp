@@ -541,7 +541,7 @@ __device__ void KFringeFwd<D, SPLIT, WRAP>::run(const FwdArgs& args, const Blk& 
     dnu[c] = args.dnu[fl];
     csc[c] = SPLIT ? chan_scale(args.cscale, fl, d_omega) : 1.0f;   // power of two
     const float sig = fwhm[0] * args.sigr[fl];
-    kb[c] = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
+    kb[c] = beam_kb(sig);
     cut = c == 0 ? beam_cut(args.cut_sig2, sig) : fmaxf(cut, beam_cut(args.cut_sig2, sig));
     imf[c] = img + static_cast<size_t>(fl) * nvp;
   }
@@ -1029,7 +1029,7 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
     chan_on[c] = fc < nf ? 1.0f : 0.0f;
     dnu[c] = args.dnu[fch[c]];
     const float sig = fw * args.sigr[fch[c]];
-    kb[c] = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
+    kb[c] = beam_kb(sig);
     cut = c == 0 ? beam_cut(args.cut_sig2, sig) : fmaxf(cut, beam_cut(args.cut_sig2, sig));
     acc_i[c] = acc_f[c] = 0.f;
   }

@@ -13,6 +13,7 @@
 // Where the response is negligible the ratio only amplifies noise (it grows
 // like 1 / B), so pixels whose weight is below kMapWeightFloor times the
 // channel's largest weight map to 0, as do pixels never above the horizon.
+#include "beam.hpp"
 #include "objects.hpp"
 
 namespace bv {
@@ -38,9 +39,7 @@ k_map_weight(int nf, int nv, int nvp, int nant, double d_omega, const float* __r
   double s2[kMapChan], s4[kMapChan];
 #pragma unroll
   for (int c = 0; c < kMapChan; ++c) {
-    const float sig = fwhm[0] * sigr[min(f0 + c, nf - 1)];
-    const float kb = 1.0f / (2.0f * sig * sig * static_cast<float>(kLn2));
-    kb2[c] = -2.0f * kb;
+    kb2[c] = -2.0f * beam_kb(fwhm[0] * sigr[min(f0 + c, nf - 1)]);
     s2[c] = s4[c] = 0.0;
   }
   for (int a = lane; a < nant; a += 64)
