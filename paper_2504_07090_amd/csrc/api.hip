@@ -33,17 +33,16 @@ void adjoint_tail(const vis_field* f, const float* fwhm, float* grad_alm, float2
     launch_fringe_adj(f, f->scr.img, fwhm, f->scr.gco, full ? nullptr : f->scr.dimg, f->scr.f_part, s,
                       full ? f->scr.sep_dfull : nullptr);
   }
-  {
-    // one launch for the gain gradient, chi^2 and dL/dF (the gains pass's
-    // partials are complete before the fringe pass, dL/dF's after it)
-    StageScope sc(kStageReduce);
-    launch_reduce_grads(f, with_chi2, f->scr.chi_part, chi2, f->scr.g_part, grad_gains, f->scr.f_part,
-                        grad_fwhm, s);
-  }
   if (grad_alm != nullptr) {
     StageScope sc(kStageSynthAdj);
     launch_synth_adj(f, full ? nullptr : f->scr.dimg, fwhm, grad_alm, s);
   }
+  // one launch for the gain gradient, chi^2 and dL/dF (the gains pass's
+  // partials are complete before the fringe pass, dL/dF's after it), after
+  // everything that reads the beam width: grad_fwhm may be the same address
+  StageScope sc(kStageReduce);
+  launch_reduce_grads(f, with_chi2, f->scr.chi_part, chi2, f->scr.g_part, grad_gains, f->scr.f_part,
+                      grad_fwhm, s);
 }
 
 }  // namespace bv
