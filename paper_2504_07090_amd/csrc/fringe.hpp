@@ -942,7 +942,8 @@ constexpr int kAdjRounds = 3;
 template <int D, bool SPLIT, bool WRAP>
 struct KFringeAdj {
   using Args = AdjArgs;
-  static constexpr int kThreads = 64 * adj_waves(D), kWaves = 1;
+  // four waves per SIMD, where the compiler would take one register too many
+  static constexpr int kThreads = 64 * adj_waves(D), kWaves = D == 4 && SPLIT ? 4 : 1;
   static __device__ void run(const AdjArgs& args, const Blk& B);
 };
 
@@ -978,6 +979,12 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
   // beta-axis terms in the tile's row 2 D (the gains pass put omega(0, m)
   // there) against a row of ones in the pixel operand
   constexpr bool AXT = adj_axis_in_tile(D);
+  // the beam weights of two channels in the padding of the split B rows: with an
+  // array of their own a block's LDS fits a CU three times instead of four (19
+  // dishes, 120 channels, 30 times: 128 -> 107 us with a 10 deg beam, 355 -> 315 us
+  // with 37 deg; where four fit either way the array's reads are 2% faster)
+  constexpr bool BW_PAD = SPLIT && NCH == 2;
+  static_assert(!BW_PAD || 2 * NCH <= R::BH - W / 2, "beam weights in the padding of the split rows");
   const int nfg = (nf + NCH - 1) / NCH;   // channel groups
   // dL/dI of this lane's pixel of a chunk
   auto put = [&](int chunk, int f, float v) {
@@ -1050,8 +1057,12 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
   // alpha-axis terms of the pixels of the four 16-pixel groups, weighted by B
   // and by B theta^2; reduced across the row groups once, after the time loop.
   float pz_i[4] = {0.f, 0.f, 0.f, 0.f}, pz_f[4] = {0.f, 0.f, 0.f, 0.f};
-  __shared__ float2 BW_all[NW][NCH][64];   // (B, B theta^2) of every pixel of the chunk at this t
-  float2 (*BW)[64] = BW_all[wv];
+  // (B, B theta^2) of every pixel of the chunk at this t and channel
+  __shared__ float2 BW_all[BW_PAD ? 1 : NW][NCH][BW_PAD ? 1 : 64];
+  auto bw_at = [&](int c, int px) -> float2& {
+    if constexpr (BW_PAD) return *reinterpret_cast<float2*>(Bh + px * R::BH + W / 2 + 2 * c);
+    else return BW_all[wv][c][px];
+  };
   const size_t gst = static_cast<size_t>(nf) * gstride;
   // gco feeds the wave-uniform (scalar) loads of the axis coefficients;
   // gco_lane, the same table, the per-lane loads of the prefetch below: a
@@ -1151,10 +1162,10 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
         powers_split_adj<D>(av + 2 * D * c, bh + D * c, bl + D * c, c1, s1, c2, s2, visit);
         // T comes out scaled by the coefficients' power of two: the weights undo it
         const float isc = G[NMAT + 16 * RT + 4 * D];
-        BW[c][lane] = make_float2(bm[c] * isc, bm[c] * th2 * isc);
+        bw_at(c, lane) = make_float2(bm[c] * isc, bm[c] * th2 * isc);
       } else {
         powers_f32<D>(av + 2 * D * c, bv + 2 * D * c, c1, s1, c2, s2, 1.0f, visit);
-        BW[c][lane] = make_float2(bm[c], bm[c] * th2);
+        bw_at(c, lane) = make_float2(bm[c], bm[c] * th2);
       }
     }
     if constexpr (SPLIT) {
@@ -1173,7 +1184,7 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
     wave_sync();
     float2 bw[4];
 #pragma unroll
-    for (int pg = 0; pg < 4; ++pg) bw[pg] = BW[NCH == 1 ? 0 : c_out][16 * pg + (lane & 15)];
+    for (int pg = 0; pg < 4; ++pg) bw[pg] = bw_at(NCH == 1 ? 0 : c_out, 16 * pg + (lane & 15));
     // T = G Bb + alpha-axis rows for the four 16-pixel groups: the four MFMA
     // chains are interleaved (pixel group innermost) so consecutive MFMAs are
     // independent
