@@ -203,11 +203,12 @@ struct HostGeometry {
   std::vector<double> p1, p2;            // [t][nv_pad]
   std::vector<float> th2;                // [t][nv_pad]
   std::vector<int> tlo, thi;             // per chunk
-  // CSR lists in ascending order of the excess theta^2 of the chunk's nearest
-  // pixel over the nearest pixel of the sky at that time: the chunks up at
-  // each time, and the times at which each chunk is up
-  std::vector<int> tchunk_off, tchunk, ctime_off, ctime;
+  // lists in ascending order of the excess theta^2 of the chunk's nearest pixel
+  // over the nearest pixel of the sky at that time: the chunks up at each time
+  // (CSR), and the times at which each chunk is up (a row of n_time per chunk)
+  std::vector<int> tchunk_off, tchunk, ctime;
   std::vector<float> tchunk_ex, ctime_ex, chunk_ex;   // chunk_ex: a chunk's smallest ctime_ex
+  std::vector<int4> chunk_times;
   double vis_pix_time = 0.0;             // sum over t of visible pixel count
   double beam_bits = kBeamBits;          // of the beam cut
 };
@@ -500,21 +501,30 @@ static HostGeometry build_geometry(const vis_basis* basis, const vis_field_desc*
       }
     }
   }
-  auto flatten = [](std::vector<std::vector<std::pair<float, int>>>& rows, std::vector<int>& off,
-                    std::vector<int>& idx, std::vector<float>& ex) {
-    off.push_back(0);
-    for (auto& r : rows) {
-      std::sort(r.begin(), r.end());
-      for (const auto& v : r) {
-        ex.push_back(v.first);
-        idx.push_back(v.second);
-      }
-      off.push_back(static_cast<int>(idx.size()));
+  g.tchunk_off.push_back(0);
+  for (auto& r : by_time) {
+    std::sort(r.begin(), r.end());
+    for (const auto& v : r) {
+      g.tchunk_ex.push_back(v.first);
+      g.tchunk.push_back(v.second);
     }
-  };
-  flatten(by_time, g.tchunk_off, g.tchunk, g.tchunk_ex);
-  flatten(by_chunk, g.ctime_off, g.ctime, g.ctime_ex);
-  for (int c = 0; c < nchunks; ++c) g.chunk_ex.push_back(g.ctime_ex[g.ctime_off[c]]);
+    g.tchunk_off.push_back(static_cast<int>(g.tchunk.size()));
+  }
+  g.ctime.assign(static_cast<size_t>(nchunks) * nt, 0);
+  g.ctime_ex.assign(g.ctime.size(), kBelowHorizon);
+  for (int c = 0; c < nchunks; ++c) {
+    auto& r = by_chunk[c];
+    std::sort(r.begin(), r.end());
+    for (size_t i = 0; i < r.size(); ++i) {
+      g.ctime_ex[static_cast<size_t>(c) * nt + i] = r[i].first;
+      g.ctime[static_cast<size_t>(c) * nt + i] = r[i].second;
+    }
+    int4 ct = make_int4(0, 0, static_cast<int>(r.size()), r.back().second);
+    std::memcpy(&ct.x, &r.front().first, sizeof(float));
+    std::memcpy(&ct.y, &r.back().first, sizeof(float));
+    g.chunk_times.push_back(ct);
+    g.chunk_ex.push_back(r.front().first);
+  }
   return g;
 }
 
@@ -531,9 +541,9 @@ static void carve_field(vis_field* f, Carver& cv, int n_tchunk) {
   T.tchunk_off = cv.take<int>(nt + 1);
   T.tchunk = cv.take<int>(std::max(1, n_tchunk));
   T.tchunk_ex = cv.take<float>(std::max(1, n_tchunk));
-  T.ctime_off = cv.take<int>(f->n_chunks + 1);
-  T.ctime = cv.take<int>(std::max(1, n_tchunk));
-  T.ctime_ex = cv.take<float>(std::max(1, n_tchunk));
+  T.chunk_times = cv.take<int4>(f->n_chunks);
+  T.ctime = cv.take<int>(static_cast<size_t>(f->n_chunks) * nt);
+  T.ctime_ex = cv.take<float>(static_cast<size_t>(f->n_chunks) * nt);
   T.chunk_ex = cv.take<float>(f->n_chunks);
   T.bl_ant = cv.take<int2>(f->n_bl);
   T.bl_u = cv.take<int>(f->n_bl);
@@ -842,7 +852,7 @@ vis_status vis_field_create(const vis_basis* basis, const vis_field_desc* desc, 
     up(T.tchunk_off, g.tchunk_off, s);
     up(T.tchunk, g.tchunk, s);
     up(T.tchunk_ex, g.tchunk_ex, s);
-    up(T.ctime_off, g.ctime_off, s);
+    up(T.chunk_times, g.chunk_times, s);
     up(T.ctime, g.ctime, s);
     up(T.ctime_ex, g.ctime_ex, s);
     up(T.chunk_ex, g.chunk_ex, s);

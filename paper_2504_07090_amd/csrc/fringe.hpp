@@ -891,11 +891,11 @@ __device__ void KFringeFwd<D, SPLIT, WRAP>::run(const FwdArgs& args, const Blk& 
 // beam: 0.660 -> 0.212 ms for 27% of the (chunk, time) pairs.  What is left
 // over the 0.176 ms of the same time per pair is each wave's start and end
 // (about 200 vector instructions, two steps' worth).  Tried: one wave per item
-// at every beam width (0.245 ms: 8400 items within the beam in 4096 resident
-// waves of unequal length leave CUs idle at the end, 72% of the CU cycles
-// busy), two waves (0.215 ms), and resident blocks that take items in rounds
-// (0.236 ms); with a 35 deg beam one wave per item is the fastest (37 dishes:
-// 0.210 ms against 0.227 ms with four waves), hence the rule on the items.
+// (0.245 ms: 8400 items within the beam in 4096 resident waves of unequal length
+// leave CUs idle at the end, 72% of the CU cycles busy), two waves (0.215 ms), and
+// resident blocks that take items in rounds (0.236 ms).  Chunks dealt to the XCDs
+// with all their channels, so that a chunk's geometry is read into one L2 only,
+// change nothing (0.99 to 1.01 times over beams of 10 to 37 deg).
 //
 // SPLIT: T = G Bb runs on FP16 MFMA, per 16 x 16 tile one K = 32 product
 // [G_hi | G_lo] [B_hi; B_hi] and one K = 16 product G_hi B_lo; the coefficient
@@ -914,8 +914,9 @@ struct AdjArgs {
   const float* chunk_ex;
   float sigr_max;
   int split_chunks;
+  int shared_items;     // items of the first split_chunks chunks
   unsigned nfg_magic;   // ceil(2^32 / channel groups)
-  const int* ctime_off;
+  const int4* chunk_times;
   const int* ctime;
   const float* ctime_ex;
   const float* img;
@@ -931,13 +932,24 @@ struct AdjArgs {
   int nv, fstride;
 };
 
-// Wavefronts per block, and the rounds of resident waves that the items within
-// the beam must exceed for each wave to take whole items.
+// Wavefronts per block.
 __host__ __device__ constexpr int adj_waves(int D) { return D <= 8 ? 4 : 2; }
-// Below four times per wave a shared item is mostly its set-up and the waves'
-// reduction: they share only what one round of resident blocks holds (61 dishes,
-// 30 channels, 4 times, 31 deg beam: 50 us shared, 33 us not).
-constexpr int kAdjRounds = 3;
+
+// Items within the beam up to which a block's waves share one item's times:
+// rounds of `resident` waves, more of them the more times an item may have.  A
+// wave that takes items of its own leaves its SIMD idle for part of the last
+// item's times; sharing costs every item its set-up in each wave and the
+// reduction over them.  With `n` rounds of items, microseconds whole / shared:
+//   61 dishes, 15 times  n = 0.2: 19.1 / 14.6   0.6: 30.7 / 30.4   1.1: 45.7 / 50.2   2.9 (24 deg): 120 / 132
+//   61 dishes, 30 times  n = 0.5: 40.8 / 35.9   1.6: 101 / 101     1.9: 124 / 120     3.1 (14 deg): 181 / 187
+//   61 dishes, 60 times  n = 0.7: 102 / 87      1.3: 159 / 139     4.0 (24 deg): 437 / 405
+//   61 dishes,  5 times  n = 0.2: 10.3 / 10.1   0.6: 15.0 / 19.2
+//   91 dishes, 30 times  n = 1.4: 156 / 123     3.1: 288 / 258     4.7: 372 / 363     7.8 (24 deg): 587 / 591
+//   91 dishes,  5 times  n = 2.1: 44 / 48       4.5: 82 / 89
+inline double adj_shared_items(int D, int n_time, int resident) {
+  const double t = n_time;
+  return resident * (D <= 8 ? std::max(t / 25.0, t * t / 350.0) : t / 4.0);
+}
 
 template <int D, bool SPLIT, bool WRAP>
 struct KFringeAdj {
@@ -1003,16 +1015,20 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
   // of the field's widest channel are a prefix, the longest time loops start
   // first, and the grid ends on items that only write zeros.  With few items
   // within the beam (at most split_chunks chunks) the block's waves share one
-  // item's times; with many, each wave takes an item of its own.
-  const bool shared = args.split_chunks >= nchunks || args.chunk_ex[args.split_chunks] > cut_w;
-  const int item = shared ? B.x : B.x * NW + wv;
+  // item's times; with many, each wave takes an item of its own, and so it does
+  // of the items that are then sure to be outside.
+  const bool few = args.split_chunks >= nchunks || args.chunk_ex[args.split_chunks] > cut_w;
+  const bool shared = few && B.x < args.shared_items;
+  const int first = few ? args.shared_items : 0;   // of the items taken by waves
+  const int item = shared ? B.x : first + (B.x - first) * NW + wv;
   if (item >= nfg * nchunks) return;
   // item / nfg through the host's ceil(2^32 / nfg) (at most one too large), on
   // the scalar unit
   int chunk = nfg == 1 ? item : static_cast<int>(__umulhi(static_cast<unsigned>(item), args.nfg_magic));
   if (chunk * nfg > item) --chunk;
   const int fgrp = item - chunk * nfg;
-  if (args.chunk_ex[chunk] > cut_w) {   // uniform over the wave
+  const int4 ct = args.chunk_times[chunk];
+  if (__int_as_float(ct.x) > cut_w) {   // uniform over the wave
     if (!shared || wv == 0)
 #pragma unroll
       for (int c = 0; c < NCH; ++c) {
@@ -1046,12 +1062,16 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
   // its output rows 4 (lane >> 4) .. + 3 belong to channel (lane >> 4) / 2
   const int c_row = NCH > 1 ? (lane & 15) / (2 * D) : 0;
   const int c_out = NCH > 1 ? (lane >> 4) / (D / 2) : 0;
-  // the times at which this chunk is within the beam of the group's widest channel
-  const int tbeg = args.ctime_off[chunk], tall = args.ctime_off[chunk + 1] - tbeg;
-  const int* __restrict__ tlist = args.ctime + tbeg;
-  // 64 entries of the list in the lanes: the first ones load beside their excesses
-  int tl = tlist[min(lane, tall - 1)], tl_blk = 0;
-  const int ntl = beam_prefix<1>(args.ctime_ex + tbeg, tall, cut, lane);
+  // the times at which this chunk is within the beam of the group's widest
+  // channel; where that is all of them, nothing waits for the list's excesses
+  // (nor, in a wave that takes them all, the first step for the list)
+  const int tall = ct.z;
+  const size_t trow = static_cast<size_t>(chunk) * args.nt;
+  const int* __restrict__ tlist = args.ctime + trow;
+  int tl = tlist[min(lane, args.nt - 1)], tl_blk = 0;   // 64 entries of the list in the lanes
+  const bool all_in = __int_as_float(ct.y) <= cut;
+  int ntl = tall;
+  if (!all_in) ntl = beam_prefix<1>(args.ctime_ex + trow, tall, cut, lane);
   const int mine = shared ? max(0, (ntl - wv + NW - 1) / NW) : ntl;   // entries w0, w0 + nw, ..
   // Partial sums, over this lane's four rows of every row tile, of the core and
   // alpha-axis terms of the pixels of the four 16-pixel groups, weighted by B
@@ -1095,8 +1115,7 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
     return __builtin_amdgcn_readlane(tl, e & 63);
   };
   LaneOffset<(D <= 6)> lo(lane);
-  auto load_step = [&](Step& S, int i) {
-    const int t = time_at(i);
+  auto load_step = [&](Step& S, int t) {   // t uniform
     lo.touch(t);
     S.t = t;
     const size_t row = static_cast<size_t>(t) * nvp + chunk * kChunk;   // uniform over the wave
@@ -1136,7 +1155,7 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
     const float th2 = S.th2;
     // unconditional (the last step re-reads its own time) so that the waits
     // for this step's operands never cover the loads just issued
-    load_step(next, min(i + 1, mine - 1));
+    load_step(next, time_at(min(i + 1, mine - 1)));
     float av[W], bv[SPLIT ? 1 : W];
     uint32_t bh[SPLIT ? W / 2 : 1], bl[SPLIT ? W / 2 : 1];
     float bm[NCH], zax[NCH];
@@ -1254,7 +1273,9 @@ __device__ void KFringeAdj<D, SPLIT, WRAP>::run(const AdjArgs& args, const Blk& 
   };
   if (mine > 0) {   // uniform over the wave
     Step sa, sb;
-    load_step(sa, 0);
+    int t_first = ct.w;
+    if (!all_in || shared) t_first = time_at(0);
+    load_step(sa, t_first);
     for (int i = 0; i < mine; i += 2) {
       step(i, sa, sb);
       if (i + 1 >= mine) break;
@@ -1336,17 +1357,22 @@ static void adj_d(const vis_field* f, const float* img, const float* fwhm, const
                   float* dimg, float* dfull, float* f_part, hipStream_t st) {
   constexpr int nch = adj_channels_per_tile(D);
   const int nfg = (f->n_freq + nch - 1) / nch;
-  const int nblk = static_cast<int>(round_up(static_cast<long>(nfg) * f->n_chunks, 8));
   const int waves = f->n_cu * (D <= 8 ? 16 : 8);   // resident
-  const int split_chunks = (f->n_time >= 4 * adj_waves(D) ? kAdjRounds * waves : waves / adj_waves(D)) / nfg;
+  const int split_chunks =
+      static_cast<int>(std::min<double>(f->n_chunks, adj_shared_items(D, f->n_time, waves) / nfg));
+  // blocks for either way of taking the items, the later ones of which are idle
+  // in the other (a block that only finds that out holds its LDS for a quarter
+  // of a microsecond)
+  const int items = nfg * f->n_chunks, shared_items = nfg * split_chunks;
+  const int nblk = static_cast<int>(round_up(shared_items + ceil_div(items - shared_items, adj_waves(D)), 8));
   const auto& T = f->tab;
   ProfScope ps(&f->prof, "k_fringe_adj", st);
   BV_REQUIRE(f->dtile == D, VIS_EINVAL, "internal: adjoint tile mismatch");
   BV_REQUIRE((dimg == nullptr) != (dfull == nullptr), VIS_EINVAL, "internal: one adjoint output");
   const AdjArgs a{f->n_freq, f->n_time, f->nv_pad, f->n_chunks, f->gstride,
                   static_cast<float>(f->d_omega), f->cut_sig2, T.dnu, T.sigr, T.q1, T.q2, T.th2,
-                  T.chunk_ex, f->sigr_max, split_chunks,
-                  static_cast<unsigned>(((1ull << 32) + nfg - 1) / nfg), T.ctime_off, T.ctime, T.ctime_ex, img, fwhm, gco, gco, dimg, f_part, dfull, T.sep_voff, f->nv,
+                  T.chunk_ex, f->sigr_max, split_chunks, shared_items,
+                  static_cast<unsigned>(((1ull << 32) + nfg - 1) / nfg), T.chunk_times, T.ctime, T.ctime_ex, img, fwhm, gco, gco, dimg, f_part, dfull, T.sep_voff, f->nv,
                   f->basis->nphi_b};
   const bool wrap = f->max_turns > kMaxTurns;
   auto launch = [&](auto k) { launch_k<typename decltype(k)::Kernel>(dim3(nblk), 0, a, st, "k_fringe_adj"); };

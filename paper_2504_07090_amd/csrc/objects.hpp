@@ -105,9 +105,11 @@ struct FieldTables {
   int* tchunk = nullptr;           // [sum] chunk indices, ascending tchunk_ex per time
   float* tchunk_ex = nullptr;      // [sum] theta^2 of the chunk's nearest pixel above the horizon
                                    //   minus that of the nearest pixel of the sky, at that time
-  int* ctime_off = nullptr;        // [n_chunks + 1] CSR of the times at which each chunk is active
-  int* ctime = nullptr;            // [sum] time indices, ascending ctime_ex per chunk
-  float* ctime_ex = nullptr;       // [sum] the same excess
+  int4* chunk_times = nullptr;     // [n_chunks] smallest and largest excess of the chunk's active times
+                                   //   (bits of the floats), their number, the time of the largest
+  int* ctime = nullptr;            // [n_chunks][n_time] active times of each chunk, ascending ctime_ex,
+                                   //   then zeros
+  float* ctime_ex = nullptr;       // [n_chunks][n_time] the same excess
   float* chunk_ex = nullptr;       // [n_chunks] each chunk's smallest excess, ascending
   int2* bl_ant = nullptr;          // [n_bl] (i, j)
   int* bl_u = nullptr;             // [n_bl] unique index, negative-encoded sign: u or ~u
