@@ -33,16 +33,20 @@ void adjoint_tail(const vis_field* f, const float* fwhm, float* grad_alm, float2
     launch_fringe_adj(f, f->scr.img, fwhm, f->scr.gco, full ? nullptr : f->scr.dimg, f->scr.f_part, s,
                       full ? f->scr.sep_dfull : nullptr);
   }
+  {
+    // one launch for the gain gradient, chi^2 and dL/dF (the gains pass's
+    // partials are complete before the fringe pass, dL/dF's after it), while the
+    // partials are in cache: after a dense synthesis adjoint, which streams Y, it
+    // takes 9.7 us instead of 7.2.  It keeps the beam width in the scratch, since
+    // grad_fwhm may be the width's own address
+    StageScope sc(kStageReduce);
+    launch_reduce_grads(f, with_chi2, f->scr.chi_part, chi2, f->scr.g_part, grad_gains, f->scr.f_part,
+                        fwhm, grad_fwhm, s);
+  }
   if (grad_alm != nullptr) {
     StageScope sc(kStageSynthAdj);
-    launch_synth_adj(f, full ? nullptr : f->scr.dimg, fwhm, grad_alm, s);
+    launch_synth_adj(f, full ? nullptr : f->scr.dimg, f->scr.width, grad_alm, s);
   }
-  // one launch for the gain gradient, chi^2 and dL/dF (the gains pass's
-  // partials are complete before the fringe pass, dL/dF's after it), after
-  // everything that reads the beam width: grad_fwhm may be the same address
-  StageScope sc(kStageReduce);
-  launch_reduce_grads(f, with_chi2, f->scr.chi_part, chi2, f->scr.g_part, grad_gains, f->scr.f_part,
-                      grad_fwhm, s);
 }
 
 }  // namespace bv
@@ -123,7 +127,7 @@ vis_status chi2_and_grad(const vis_field* f, const vis_c64* data, float sigma_n,
     const bool any_grad = grad_alm || grad_gains || grad_fwhm;
     if (!any_grad) {
       StageScope sc(kStageReduce);
-      launch_reduce_grads(f, true, f->scr.chi_part, chi2, nullptr, nullptr, nullptr, nullptr, s);
+      launch_reduce_grads(f, true, f->scr.chi_part, chi2, nullptr, nullptr, nullptr, nullptr, nullptr, s);
       return;
     }
     adjoint_tail(f, fwhm, grad_alm, reinterpret_cast<float2*>(grad_gains), grad_fwhm, true, chi2, s);

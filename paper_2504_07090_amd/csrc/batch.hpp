@@ -90,7 +90,7 @@ k_many(const typename K::Args* __restrict__ args, const BatchEntry* __restrict__
 // Stages of one evaluation, in execution order.
 enum Stage : int {
   kStageSynthFwd = 0, kStageFringeFwd = 1, kStageGains = 2, kStageFringeAdj = 3,
-  kStageSynthAdj = 4, kStageReduce = 5, kNumStages = 6
+  kStageReduce = 4, kStageSynthAdj = 5, kNumStages = 6
 };
 
 // One recorded launch (type-erased).

@@ -589,6 +589,7 @@ static void carve_field(vis_field* f, Carver& cv, int n_tchunk) {
   S.chi_part = cv.take<double>(nt * nfq);
   S.g_part = cv.take<float2>(nt * nfq * f->n_ant);
   S.f_part = cv.take<float>(nfq * f->n_chunks);
+  S.width = cv.take<float>(1);
   if (dense)
     S.a_part = cv.take<float>(std::max(static_cast<size_t>(f->asplit) * nfq * kpad,
                                        static_cast<size_t>(f->fsplit) * nfq * nvp));

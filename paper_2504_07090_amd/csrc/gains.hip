@@ -800,6 +800,8 @@ struct ReduceArgs {
   const float2* g_part;
   float2* grad_gains;
   const float* f_part;
+  const float* fwhm;    // may be the address of grad_fwhm
+  float* width;
   float* grad_fwhm;
 };
 
@@ -858,9 +860,12 @@ __device__ void KReduceGrads::run(const ReduceArgs& a, const Blk& B) {
       const double tot = block_sum(chi_part, nt * nf, red);
       if (tid == 0) *chi2 = tot;
     }
-  } else if (grad_fwhm != nullptr) {
-    const double tot = block_sum(f_part, nfpart, red);
-    if (tid == 0) *grad_fwhm = static_cast<float>(tot);
+  } else {
+    if (a.fwhm != nullptr && tid == 0) *a.width = *a.fwhm;
+    if (grad_fwhm != nullptr) {
+      const double tot = block_sum(f_part, nfpart, red);
+      if (tid == 0) *grad_fwhm = static_cast<float>(tot);
+    }
   }
 }
 
@@ -963,11 +968,11 @@ void launch_gains(const vis_field* f, GainMode mode, const float2* vu, const flo
 
 void launch_reduce_grads(const vis_field* f, bool with_chi2, const double* chi_part, double* chi2,
                          const float2* g_part, float2* grad_gains, const float* f_part,
-                         float* grad_fwhm, hipStream_t st) {
+                         const float* fwhm, float* grad_fwhm, hipStream_t st) {
   const int nblk = (grad_gains != nullptr ? ceil_div(static_cast<long>(f->n_freq) * f->n_ant, 1024 / 8) : 0) + 2;
   ProfScope ps(&f->prof, "k_reduce_grads", st);
   const ReduceArgs a{f->n_time, f->n_freq, f->n_ant, f->n_freq * f->n_chunks, with_chi2 ? 1 : 0,
-                     chi_part, chi2, g_part, grad_gains, f_part, grad_fwhm};
+                     chi_part, chi2, g_part, grad_gains, f_part, fwhm, f->scr.width, grad_fwhm};
   launch_k<KReduceGrads>(dim3(nblk), 0, a, st, "k_reduce_grads");
 }
 

@@ -86,6 +86,7 @@ struct FieldScratch {
   double* chi_part = nullptr;      // [n_time * n_freq]
   float2* g_part = nullptr;        // [n_time][n_freq][n_ant]
   float* f_part = nullptr;         // [n_freq * n_chunks]
+  float* width = nullptr;          // the beam width of this evaluation, kept by the gradient reduction
   float* a_part = nullptr;         // split-K partials: [asplit][n_freq][kpad] of dL/da,
                                    // or [fsplit][n_freq][nv_pad] of the sky
 };
@@ -243,7 +244,7 @@ void launch_gains(const vis_field* f, GainMode mode, const float2* vu, const flo
                   float* gco, float2* g_part, hipStream_t st);
 void launch_reduce_grads(const vis_field* f, bool with_chi2, const double* chi_part,
                          double* chi2, const float2* g_part, float2* grad_gains,
-                         const float* f_part, float* grad_fwhm, hipStream_t st);
+                         const float* f_part, const float* fwhm, float* grad_fwhm, hipStream_t st);
 
 // The evaluation sequences shared by the entry points: sky synthesis and the
 // forward fringe pass into the field's scratch (img, vu); and, once the gains
