@@ -20,11 +20,12 @@
 // in registers and LDS; nothing of size pixels x baselines touches HBM.
 //
 // Phase accuracy: x = nu (e . s) / c comes from tables reduced modulo one cycle
-// in FP64 (reduced_cycles), and the powers alpha^n, n <= D, from two chains of
-// the three-term recurrence (lattice_powers).  A rounding error made at step k
-// of a chain reaches step j multiplied by sin((j - k) 2t) / sin(2t), at most
-// j - k in size, so the error of alpha^n stays below about n^2 / 8 FP32
-// roundings (8 at n = 8).
+// in FP64 (phase_cycles), and the powers alpha^n, n <= D, from two chains of the
+// three-term recurrence (lattice_powers).  A rounding error made at step k of a
+// chain reaches step j multiplied by sin((j - k) 2t) / sin(2t), at most j - k in
+// size, so the error of alpha^n stays below about n^2 / 8 FP32 roundings (8 at
+// n = 8).  The split kernels take one chain (StepChain): n^2 / 2, 72 roundings
+// or 4e-6 at n = 12 and 8e-6 at n = 16, against bounds of 1e-4 on what they form.
 //
 // The adjoint (transpose over the reals) of the same map, for coefficients
 // omega_u = dL/dRe V_u - i dL/dIm V_u (formed by the gains pass), is
@@ -104,10 +105,11 @@ struct LaneOffset {
 // Phase of nu_f p in cycles, modulo whole cycles, in FP32 from the table entry
 // q = (y, p), y = nu_c p reduced modulo 1 on the host in FP64, and dnu = nu_f -
 // nu_c: x = y + dnu p, one fma.  The hardware sine and cosine take an argument
-// of up to 256 turns and reduce it exactly (errors on [-2, 2] as on [-1/2,
-// 1/2], measured), so only fields whose |dnu p| may exceed kMaxTurns (WRAP: a
-// lattice step of a kilometre over a half band of 75 MHz) reduce it here; the
-// two instructions per axis cost 3% of both passes.
+// of up to 256 turns and reduce it exactly (errors on [-2, 2] as on [-1/2, 1/2],
+// measured; at 30, 150 and 230 turns the visibilities follow the rounding of x
+// itself, as they do reduced at 400), so only fields whose |x| may exceed kMaxTurns
+// (WRAP: a lattice step of a kilometre over a half band of 75 MHz) reduce it here;
+// the two instructions per axis cost 3% of both passes.
 constexpr float kMaxTurns = 240.0f;
 template <bool WRAP>
 __device__ __forceinline__ float phase_cycles(float dnu, float2 q) {
