@@ -309,8 +309,9 @@ __device__ __forceinline__ void write_coefficients(const GainArgs& a, const floa
 // two antennas' gradients and stores them in LDS at the baseline's positions
 // in the per-unique and per-antenna lists, so the sums that follow run over
 // contiguous LDS ranges.  Fields beyond KGainsStaged's limits run one slice per
-// block, and their sums walk the lists and recompute the terms.  Each list gets `w` lanes that combine their
-// partial sums with a fixed butterfly, so every result has a fixed order.
+// block, and their sums walk the lists and recompute the terms.  Each list gets
+// `w` lanes that combine their partial sums with a fixed butterfly, so every
+// result has a fixed order.
 constexpr int kGainsMaxPerThread = 8;
 
 template <bool SORTED, int MODE>
@@ -558,15 +559,16 @@ __device__ void KGains<SORTED, MODE>::run(const GainArgs& a, const Blk& B) {
 
 // Staged gains pass: one block per channel and slab of times, each thread with
 // the packed table entries of its baselines (tid + NT q) in registers for the
-// slab (512 threads of up to 9 baselines, or 1024 of up to 8).  Per slice the threads form every baseline's cotangent once, from
-// coalesced loads issued in the slice before, and its terms: first the omega
-// term goes to LDS in u_list order and 16 lanes per unique baseline add its
-// range (lists in descending length, so that the four groups of a wave are
-// equally long); then h = c conj(V) takes its place in the lexicographic order
+// slab (256 or 1024 threads of up to 8 baselines, or 512 of up to 9).  Per slice
+// the threads form every baseline's cotangent once, from coalesced loads issued in
+// the slice before, and its terms: first the omega term goes to LDS in u_list
+// order and 16 lanes per unique baseline add its range (lists in descending
+// length, so that the four groups of a wave are equally long); then h = c conj(V) takes its place in the lexicographic order
 // of the baselines, and 16 lanes per antenna a add sum_b H_ab g_b, H_ab = h_ab
 // for b > a and conj(h_ba) for b < a, at indices advanced from a and b.  Sums over
 // 16 lanes run on the row-rotating vector operations.  Taken where SORTED's three
-// staged terms per baseline do not fit (62 to 128 dishes); the list walks in
+// staged terms per baseline do not fit (62 to 128 dishes) or the unique baselines
+// are more than its 256 threads (irregular arrays of fewer); the list walks in
 // memory that such fields ran before gathered each baseline's data three times
 // with one or two lanes per list: 127 dishes, 96 channels, 97 times 1484 -> 367
 // us (600 MB of data: 128 us at a copy's rate), 91 dishes, 48 channels, 45 times
