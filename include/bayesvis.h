@@ -182,7 +182,8 @@ vis_status vis_forward(const vis_field* field, const float* alm, const vis_c64* 
  * layout as vis).  Outputs (device): grad_alm [n_freq][n_modes],
  * grad_gains [n_freq][n_ant], grad_fwhm (one float).  This is the transpose
  * of the linearised forward model (Sec. 2.3: the gradient that reverse-mode
- * AD would give), evaluated by recomputing fringe tiles.                   */
+ * AD would give), evaluated by recomputing fringe tiles.  Here and in
+ * chi2_and_grad a gradient may be written over the parameter it belongs to. */
 vis_status vis_adjoint(const vis_field* field, const float* alm, const vis_c64* gains,
                        const float* fwhm, const vis_c64* dvis, float* grad_alm,
                        vis_c64* grad_gains, float* grad_fwhm, void* stream);
