@@ -208,8 +208,10 @@ inline int adj_coef_stride(int dtile, bool split) {
 
 // Delay-filtered likelihood: scratch carved from the caller's work buffer
 // (model / cotangent visibilities, the weighted filtered residual, chi^2
-// partials per wavefront), and the two GEMM passes over frequency (with cot the
-// cotangent replaces the model in w.m).
+// partials), and the two GEMM passes over frequency (with cot the cotangent
+// replaces the model in w.m).  The residual's array is part of the size for any
+// number of channels, which also sets what the static scratch array is refused
+// for; fields of up to kFilterFusedRows channels keep the residual in LDS.
 struct FilteredWork {
   float2* m = nullptr;      // [n_time][n_freq][n_bl] model, then the cotangent
   float2* w = nullptr;      // [n_time][n_freq][n_bl] F (d - m) / N~

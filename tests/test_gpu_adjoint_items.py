@@ -35,6 +35,8 @@ CASES = {
     "whole, 70 times": [(2, 150, 70, 60.0), (4, 301, 70, 60.0), (8, 150, 70, 60.0), (12, 101, 70, 60.0)],
     "whole, some outside": [(4, 81, 5, 10.0), (6, 41, 5, 10.0), (12, 47, 6, 10.0)],
     "shared": [(4, 9, 70, 60.0), (8, 9, 70, 20.0), (12, 9, 20, 20.0)],
+    # ... by blocks, those sure to be outside by waves
+    "shared, some outside": [(4, 11, 6, 10.0), (8, 6, 5, 10.0), (12, 9, 5, 10.0)],
 }
 
 
