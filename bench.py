@@ -17,8 +17,11 @@ Headline value: fwd+adjoint complex MAC/s, one MAC being one term of the
 fringe sum for one (unique baseline, pixel above the horizon, channel, time),
 counted once for the forward and once for the adjoint contraction.  The kernels
 leave out the terms whose beam weight is below 2^-40 of the largest at that time
-and channel (a 1e-12 part of a sum whose rounding is 1e-7): the value counts the
-terms that the sum has, the rooflines only those within the beam (`within_beam`).
+and channel (a 1e-12 part of a sum whose rounding is 1e-7), four fifths of them:
+the value counts the terms that the sum has, so it is a rate of the problem, which
+can exceed what the matrix cores could do, and no rate of operations.
+`value_within_beam` and the rooflines count only the terms within the beam, and
+`ms_per_step` is the measurement behind both.
 
 Serving (`serving` key): 64 concurrent chains on uneven hex fields
 (19-127 dishes, 16-128 channels, 10-120 times, lmax 30-100), one trajectory
@@ -51,7 +54,7 @@ if ROOT not in sys.path:
 
 PEAK = {"hbm_gbs": 8000.0, "fp32_mfma_tflops": 157.3, "bf16_mfma_tflops": 2500.0,
         "fp16_mfma_tflops": 2500.0}
-BEAM_BITS = 40   # kBeamBits of csrc/common.hpp
+BEAM_BITS = 40   # kBeamBits of csrc/common.hpp, which is what the timed field (lmax 100, -30.7 deg) takes
 EPS = 0.02   # leapfrog step in units of the diagonal-Hessian scale
 
 # HBM bytes per launch of the fringe kernels on this workload, from two
@@ -59,13 +62,14 @@ EPS = 0.02   # leapfrog step in units of the diagonal-Hessian scale
 #     python3 bench.py --steps 3 --warmup 1 --no-serve --no-cpu-baseline --calibrate-copy
 # each scaled by the ratio of a 256 MiB device copy's known bytes to what the
 # same counter reads for it (profiles/fringe_c1_hbm_traffic.md).  The figure is
-# reported only while the kernel sources and build flags hash to the value it
-# was taken with.
+# reported only while the sources that set it (the kernels, the beam cut, the
+# chunks' order and lists) and the build flags hash to the value it was taken with.
 TRAFFIC = {
-    "sources": ["paper_2504_07090_amd/csrc/fringe.hpp", "paper_2504_07090_amd/csrc/common.hpp",
-                "paper_2504_07090_amd/build.py"],
-    "sha256": "0f3f0508ea77baad93c0bdfc2db4b8e2cc9299ceec8e6922f6db99d40d46a7b7",
-    "bytes_per_launch": {"k_fringe_adj": 81535693, "k_fringe_fwd": 27117442},
+    "sources": ["paper_2504_07090_amd/csrc/fringe.hpp", "paper_2504_07090_amd/csrc/beam.hpp",
+                "paper_2504_07090_amd/csrc/field.hip", "paper_2504_07090_amd/csrc/objects.hpp",
+                "paper_2504_07090_amd/csrc/common.hpp", "paper_2504_07090_amd/build.py"],
+    "sha256": "1df4c12b9944460bb3c018171e906b33e8f7f4611f9b27152ed30891699af6b5",
+    "bytes_per_launch": {"k_fringe_adj": 81466409, "k_fringe_fwd": 28086757},
 }
 
 
@@ -495,8 +499,8 @@ def main():
     dom = max(ktimes, key=lambda k: ktimes[k][1])
     dom_ms = per[dom]
     nv = fld.info.n_pix_visible
+    inside = beam_fraction(cfg)
     if dom.startswith("k_fringe"):
-        inside = beam_fraction(cfg)
         work = 4.0 * inside * fld.fwd_macs   # 2 FMA per complex x real MAC
         # split-precision fields run both fringe GEMMs on FP16 MFMA
         roof = {"bound": "mfma", "peak": PEAK["fp32_mfma_tflops"] if prec == vis.VIS_FP32
@@ -575,7 +579,8 @@ def main():
 
     line = {
         "metric": "fwd+adjoint complex MAC/s; batched-HMC grad evals/s + p50/p99 latency",
-        "value": value, "unit": "complex MAC/s", "n_gpus": 1, "steps": args.steps,
+        "value": value, "unit": "complex MAC/s", "value_counts": "terms of the sum, above the horizon",
+        "value_within_beam": inside * value, "n_gpus": 1, "steps": args.steps,
         "warmup": args.warmup, "ms_per_step": ms, "higher_is_better": True, "scaling": "weak",
         "vs_baseline": None, "dtype": "f32" if prec == vis.VIS_FP32 else args.precision,
         "data": "synthetic",

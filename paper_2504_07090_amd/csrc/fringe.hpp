@@ -942,7 +942,7 @@ __host__ __device__ constexpr int adj_waves(int D) { return D <= 8 ? 4 : 2; }
 // wave that takes items of its own leaves its SIMD idle for part of the last
 // item's times; sharing costs every item its set-up in each wave and the
 // reduction over them.  With `n` rounds of items, microseconds whole / shared:
-//   61 dishes, 15 times  n = 0.2: 19.1 / 14.6   0.6: 30.7 / 30.4   1.1: 45.7 / 50.2   2.9 (24 deg): 120 / 132
+//   61 dishes, 15 times  n = 0.2: 19.1 / 14.6   0.6: 30.7 / 30.4   1.1: 45.7 / 50.2   3.8 (24 deg): 120 / 132
 //   61 dishes, 30 times  n = 0.5: 40.8 / 35.9   1.6: 101 / 101     1.9: 124 / 120     3.1 (14 deg): 181 / 187
 //   61 dishes, 60 times  n = 0.7: 102 / 87      1.3: 159 / 139     4.0 (24 deg): 437 / 405
 //   61 dishes,  5 times  n = 0.2: 10.3 / 10.1   0.6: 15.0 / 19.2

@@ -16,7 +16,7 @@ import sys
 
 
 def _short(name: str) -> str:
-    return name.split("(")[0].replace("void ", "")[:70]
+    return name.replace("(anonymous namespace)::", "").split("(")[0].replace("void ", "")[:70]
 
 
 def summarise(path: str, command: str, top: int = 16, also=()) -> str:
@@ -62,7 +62,7 @@ def summarise_counters(path: str, command: str, top: int = 20) -> str:
     return "\n".join(out) + "\n"
 
 
-def traffic_report(fetch_csv: str, write_csv: str, command: str, kernels, sha: str,
+def traffic_report(fetch_csv: str, write_csv: str, command: str, kernels, sources, sha: str,
                    copy_kib: float = 262144.0):
     """Markdown report of HBM bytes per launch from one FETCH_SIZE and one
     WRITE_SIZE run, each scaled by what the counter reads for the run's last
@@ -92,7 +92,8 @@ def traffic_report(fetch_csv: str, write_csv: str, command: str, kernels, sha: s
         b = (f * ff + wv * fw) * 1024
         per[k] = b
         out.append(f"| `{k}` | {fn[k]} | {f:.1f} | {wv:.1f} | {b:.4g} |")
-    out += ["", f"Fringe kernel sources (fringe.hpp, common.hpp) sha256 at the time of the runs: `{sha}`.", ""]
+    names = ", ".join(s.rsplit("/", 1)[-1] for s in sources)
+    out += ["", f"sha256 of the sources that set it ({names}) at the time of the runs: `{sha}`.", ""]
     return "\n".join(out) + "\n", per
 
 
